@@ -12,10 +12,8 @@
 //
 //   pass x  (binary input): one wave per row; ballots of the sources of each
 //           64-voxel chunk give the nearest source on either side by bit scans;
-//   pass y  16 (x, z) lines of one field per block, staged in an LDS tile: D_out by
-//           FH, D_in by a bounded search around each occupied voxel (FH when an
-//           obstacle is too thick for it);
-//   pass z  the same over 16 (x, y) lines per block, writing the outputs: phi =
+//   pass y  32 (x, z) lines per block, staged in an LDS tile;
+//   pass z  the same over 32 (x, y) lines per block, writing the outputs: phi =
 //           voxel * (sqrt(D_out) - sqrt(D_in)) and/or the two squared fields.
 //
 // Compact intermediates: after every pass a voxel's value in its own field is 0 (a
@@ -23,16 +21,12 @@
 // plus its occupancy bit carries both fields: 16 bits after the x pass, 32 after the
 // y pass.
 //
-// FH with 16 lanes per line.  Each lane builds the lower envelope of the samples of
-// its band of the line (FH's stack, kept as a linked list in LDS); four rounds of
-// pairwise merges join adjacent bands.  In the dual picture the envelope is the lower
-// convex hull of the points (q, F_q), F_q = f(q) + q^2, so merging the hulls
-// of two index-separated bands only removes points near the junction: pop the left
-// tail and the right head until both turns there are strictly convex (the bridge).
-// The read-off walks the merged list; along it the cost (p - q)^2 + f(q) is
-// unimodal in the list position, so each output p starts from the winner of p - 1.
-// All tests are integer cross-multiplications: F_q < 2^20 and index differences
-// < 2^9 keep every product below 2^29.
+// Passes y and z do not build FH's envelope.  Its lists are serial chains with a branch
+// per sample: split over 16 lanes per line they took 75 us (y) and 107 us (z) of a 200^3
+// field of 40 obstacles, at 150 VALU and as many SALU instructions per output.  They use
+// the other property of the same minimisation, that the minimiser over q moves right with
+// p (transform_lines): 53 and 57 us on the same grid, VALU issue (138 instructions per 64
+// outputs, 28 us of it) and the waves' LDS latency being the bound.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -42,17 +36,20 @@
 namespace smpc {
 namespace {
 
-constexpr uint32_t kNone = 0xFFFFFFFFu;  // "no source on this line (yet)"
-constexpr int kLines = 16;               // lines per FH block
-constexpr int kG = 16;                   // lanes per line
-constexpr int kFhThreads = kLines * kG;  // 256
-constexpr int kTs = kLines + 1;          // LDS tile row stride (words), padded
-
-// Compact per-voxel records.
-//   after x: bit 15 occupied, bit 14 "no source in the row", bits 0..13 distance
-//   after y: bit 31 occupied, bit 30 "no source in the plane", bits 0..29 D
-constexpr uint16_t kXOcc = 0x8000u, kXNone = 0x4000u;
-constexpr uint32_t kYOcc = 0x80000000u, kYNone = 0x40000000u, kYVal = 0x3FFFFFFFu;
+// Compact per-voxel records: a voxel's occupancy and its distance to the nearest voxel of
+// the other kind.
+//   after x: bit 15 occupied, bits 0..14 the distance along the row
+//   after y: bit 31 occupied, bits 0..30 the squared distance in the plane
+// No such voxel: the distance is kNoDist, whose square is above any squared distance in a
+// grid (3 * 511^2 < 2^20) and, like any distance, carries through the passes that follow:
+// a result of 2^20 or more means none.
+constexpr uint16_t kXOcc = 0x8000u;
+constexpr uint32_t kYOcc = 0x80000000u;
+constexpr int kNoDist = 1254;
+constexpr uint32_t kNoneD = 1u << 20;
+static_assert((long long)kNoDist * kNoDist >= kNoneD &&
+                  3ll * (kEdtMaxSide - 1) * (kEdtMaxSide - 1) < kNoneD,
+              "kNoDist tells an absent source");
 
 // ---------------------------------------------------------------------------
 // Pass x: per voxel, the distance along its row to the nearest voxel of the other
@@ -127,7 +124,7 @@ __global__ __launch_bounds__(64 * kRowWaves) void edt_pass_x_kernel(
         int dist = 1 << 30;
         if (l >= 0) dist = p - l;
         if (r < (1 << 30)) dist = min(dist, r - p);
-        out[p] = (uint16_t)((o ? kXOcc : 0u) | (dist < (1 << 30) ? (uint32_t)dist : kXNone));
+        out[p] = (uint16_t)((o ? kXOcc : 0u) | (uint32_t)min(dist, kNoDist));
       }
     }
   }
@@ -198,7 +195,7 @@ __global__ __launch_bounds__(64 * kRowWaves) void edt_pass_x_words_kernel(
       const int l = ml ? 4 * lane + last_bit4(ml) : (o ? left_f : left_o);
       const int r = mr ? 4 * lane + first_bit4(mr) : (o ? right_f : right_o);
       const int dist = min(p - l, r - p);
-      rec[k] = (uint16_t)((o ? kXOcc : 0u) | (dist < (1 << 20) ? (uint32_t)dist : kXNone));
+      rec[k] = (uint16_t)((o ? kXOcc : 0u) | (uint32_t)min(dist, kNoDist));
     }
     uint2 out;
     out.x = (uint32_t)rec[0] | ((uint32_t)rec[1] << 16);
@@ -207,424 +204,298 @@ __global__ __launch_bounds__(64 * kRowWaves) void edt_pass_x_words_kernel(
   }
 }
 
-// ---------------------------------------------------------------------------
-// FH on a tile of kLines lines held in LDS, kG lanes per line.  Samples are of type
-// Val (uint16_t when every finite sample is below 0xFFFF, else uint32_t; the
-// all-ones value marks "no sample" and dropped points) and list links are sample
-// indices of type Link (uint8_t for lines of at most 255 samples, index 255 ending a
-// list, else uint16_t), so that more tiles fit in a CU's LDS.
-// ---------------------------------------------------------------------------
-template <class Val, class Link>
-struct Tile {
-  static constexpr int kNil = (int)(Link)(-1);  // end of a linked list
-  static constexpr uint32_t kNoVal = (Val)(-1);
-  Val* f;     // [n][kTs]: f(q); kNoVal for no sample and for points dropped
-  Link* prv;  // [n][kTs]: previous kept point of the list
-  Link* nxt;  // [n][kTs]: next kept point of the list
-};
-
-// LDS bytes of a tile of n samples per line, rounded up to whole words.
-template <class Val, class Link>
-constexpr size_t tile_bytes(int n) {
-  return ((size_t)n * kTs * (sizeof(Val) + 2 * sizeof(Link)) + 3) & ~size_t(3);
-}
-
-template <class Val, class Link>
-__device__ __forceinline__ Tile<Val, Link> carve_tile(uint32_t* lds, int n) {
-  Tile<Val, Link> t;
-  t.f = reinterpret_cast<Val*>(lds);
-  t.prv = reinterpret_cast<Link*>(t.f + n * kTs);
-  t.nxt = t.prv + n * kTs;
-  return t;
-}
-
-// Point y lies strictly below the segment from x to z (x < y < z, values F).
-__device__ __forceinline__ bool below(int x, int Fx, int y, int Fy, int z, int Fz) {
-  return (Fy - Fx) * (z - y) < (Fz - Fy) * (y - x);
-}
-
-// Band [lo, hi) of the calling thread's line: kG bands of ceil(n / kG) samples.
-struct Band {
-  int line, band, lo, hi;
-};
-__device__ __forceinline__ Band my_band(int n) {
-  Band b;
-  b.line = threadIdx.x / kG;
-  b.band = threadIdx.x % kG;
-  const int len = (n + kG - 1) / kG;
-  b.lo = min(n, b.band * len);
-  b.hi = min(n, b.lo + len);
-  return b;
-}
-static_assert((kEdtMaxSide + kG - 1) / kG <= 64, "a band's occupancy fits 64 bits");
-
-// Occupancy of the thread's band, bit q - lo (occ_bits[q] holds bit `line`).
-__device__ __forceinline__ uint64_t band_occupancy(const uint32_t* occ_bits, const Band& B) {
-  uint64_t m = 0;
-  for (int q = B.lo; q < B.hi; ++q) m |= (uint64_t)((occ_bits[q] >> B.line) & 1u) << (q - B.lo);
-  return m;
-}
-
-// Every thread of the block calls this (it holds block barriers).  The thread
-// works on line threadIdx.x / kG, band threadIdx.x % kG; `active` is false for
-// lines past the end of the grid and for lines with no output to write (a wave
-// whose lines are all inactive skips the work).  emit(p, D, occupied) receives
-// each output of the band (D = kNone when the line holds no sample).
-template <class Val, class Link, class Emit>
-__device__ __forceinline__ void tile_fh(const Tile<Val, Link>& T, int n, bool active,
-                                        const uint32_t* occ_bits, Emit&& emit) {
-  constexpr int kNil = Tile<Val, Link>::kNil;
-  constexpr uint32_t kNoVal = Tile<Val, Link>::kNoVal;
+// Whether x holds in any thread of the block (at most kWaves waves); a block barrier.
+// (__syncthreads_or costs this kernel about 40 registers and two more barriers.)
+template <int kWaves>
+__device__ __forceinline__ bool block_any(bool x) {
+  __shared__ uint32_t waves_any[kWaves];
   const int lane = threadIdx.x & 63;
-  const Band B = my_band(n);
-  const int band = B.band, lo = B.lo, hi = B.hi;
-  Val* f = T.f + B.line;
-  Link* prv = T.prv + B.line;
-  Link* nxt = T.nxt + B.line;
-  auto F = [&](int q) { return (int)f[q * kTs] + q * q; };
-
-  // Phase A: lower envelope of the band, as a list head..tail.  The samples are
-  // read kAhead at a time (the pops only overwrite samples already read).
-  constexpr int kAhead = 8;
-  int head = kNil, tail = kNil;
-  if (active) {
-    int k = 0, t = 0, Ft = 0, r = 0, Fr = 0;
-    for (int q0 = lo; q0 < hi; q0 += kAhead) {
-      uint32_t fv[kAhead];
-#pragma unroll
-      for (int j = 0; j < kAhead; ++j) fv[j] = f[min(q0 + j, hi - 1) * kTs];
-#pragma unroll
-      for (int j = 0; j < kAhead; ++j) {
-        const int q = q0 + j;
-        if (q >= hi || fv[j] == kNoVal) continue;
-        const int Fq = (int)fv[j] + q * q;
-        while (k >= 2 && !below(r, Fr, t, Ft, q, Fq)) {
-          f[t * kTs] = (Val)kNoVal;
-          t = r;
-          Ft = Fr;
-          --k;
-          if (k >= 2) {
-            r = prv[t * kTs];
-            Fr = F(r);
-          }
-        }
-        prv[q * kTs] = (Link)(k ? t : kNil);
-        if (k)
-          nxt[t * kTs] = (Link)q;
-        else
-          head = q;
-        r = t;
-        Fr = Ft;
-        t = q;
-        Ft = Fq;
-        ++k;
-      }
-    }
-    if (k) {
-      nxt[t * kTs] = (Link)kNil;
-      tail = t;
-    }
-  }
+  const bool any = __any(x);
+  if (lane == 0) waves_any[threadIdx.x / 64] = any;
   __syncthreads();
+  return __any(lane < (int)(blockDim.x / 64) && waves_any[min(lane, kWaves - 1)] != 0u);
+}
 
-  // Phase B: merge groups of s bands pairwise, s = 1, 2, 4, 8.
-#pragma unroll
-  for (int s = 1; s < kG; s <<= 1) {
-    const int rh = __shfl(head, lane + 1);
-    const int rt = __shfl(tail, lane + 1);
-    int nh = head, nt = tail;
-    if (active && (band & (2 * s - 1)) == s - 1) {
-      if (tail == kNil) {
-        nh = rh;
-        nt = rt;
-      } else if (rh != kNil) {
-        int a = tail, Fa = F(a), c = rh, Fc = F(c);
-        for (;;) {
-          bool moved = false;
-          for (;;) {  // drop the left tail while it is not strictly convex
-            const int pa = prv[a * kTs];
-            if (pa == kNil) break;
-            const int Fpa = F(pa);
-            if (below(pa, Fpa, a, Fa, c, Fc)) break;
-            f[a * kTs] = (Val)kNoVal;
-            a = pa;
-            Fa = Fpa;
-            moved = true;
-          }
-          for (;;) {  // drop the right head while it is not strictly convex
-            const int nc = nxt[c * kTs];
-            if (nc == kNil) break;
-            const int Fnc = F(nc);
-            if (below(a, Fa, c, Fc, nc, Fnc)) break;
-            f[c * kTs] = (Val)kNoVal;
-            c = nc;
-            Fc = Fnc;
-            moved = true;
-          }
-          if (!moved) break;
-        }
-        nxt[a * kTs] = (Link)c;
-        prv[c * kTs] = (Link)a;
-        nt = rt;  // the extreme points of a group are never dropped
-      }
-    }
-    const int src = lane - band + (band & ~(2 * s - 1)) + s - 1;
-    head = __shfl(nh, src);
-    tail = __shfl(nt, src);
-  }
-  __syncthreads();
+// ---------------------------------------------------------------------------
+// Passes y and z: the 1-D transform D(p) = min_q (f(q) + (p - q)^2) of 32 lines per
+// block, the line's samples in a column of an LDS tile, one half-wave ("team") of lanes
+// per group of outputs, lane l of a team on line l (each half of a wave reads one row of
+// 32 banks at a time, whatever row its lanes are at, so no read has bank conflicts).
+//
+// The minimiser of output p over q moves right as p does (the cost is a Monge array), so
+// the minimisers of outputs kLeaf apart ("cuts") are found first, those of a unit's first
+// output over the whole line, the ones between by halving, each between its neighbours'
+// minimisers; then the kLeaf outputs from one cut to the next scan the rows between the
+// two minimisers, with all their minima in registers.  A line of n outputs costs about
+// n^2 / 32 + 20 n pair evaluations instead of the n^2 of the definition, in loops without
+// data-dependent lists; all of it is integer arithmetic on 32-bit words, so the result is
+// exact.
+//
+// Tile words.  A D_out sample f(q) is stored as (f(q) + q^2) << kShift, from which
+// f(q) + (p - q)^2 follows by adding (p^2 - 2 p q) << kShift: one addition per pair.
+// f + q^2 < 2^21 - 2^18 (also where f is the square of kNoDist), so no sum leaves 31 bits.
+// The low kShift bits are free: bit 0 tells an occupied voxel and the search for a
+// minimiser adds q << 1, so that one signed minimum finds value and minimiser together
+// (the leftmost one on ties).  While D_in is computed, an occupied voxel's word is
+// the complement of its D_in sample instead (negative, a free voxel's is not).
+// ---------------------------------------------------------------------------
+constexpr int kLines = 32;              // lines per block, one per lane of a team
+constexpr int kLeaf = 8;                // outputs between two cuts
+constexpr int kPad = 3;                 // rows of "no sample" after a line
+constexpr int kShift = 10;
+constexpr int kFar = kNoDist * kNoDist;  // sample of a padding row
+static_assert((2ll * (kEdtMaxSide - 1) + 1) < (1 << kShift), "q and the flag fit the low bits");
+static_assert(((long long)kFar + (kEdtMaxSide + kPad) * (kEdtMaxSide + kPad)) << kShift < (1ll << 31),
+              "words and sums fit 31 bits");
 
-  // Phase C: a kept point near the band, then the read-off.
-  int fm = kNil, lm = kNil;
-  if (active) {
-    for (int q = lo; q < hi; ++q) {
-      if (f[q * kTs] != kNoVal) {
-        if (fm == kNil) fm = q;
-        lm = q;
-      }
-    }
-  }
-  int start = fm;
+// A team stages one unit of kPer leaves of its block's lines and searches the minimiser at
+// the unit's first output over the whole line; the cuts in between and the leaves are
+// dealt to the teams in turn (obstacles and far regions cover neighbouring outputs).
+// kPer = 1, 2, 4 for lines of up to 64, 128 and 512 samples: about eight teams (four
+// waves) per block, so that small grids still fill the chip.
+__host__ __device__ constexpr int line_leaves(int n) { return (n + kLeaf - 1) / kLeaf; }
+__host__ __device__ constexpr int unit_leaves(int n) { return n <= 64 ? 1 : n <= 128 ? 2 : 4; }
+__host__ __device__ constexpr int line_waves(int n) {
+  return ((line_leaves(n) + unit_leaves(n) - 1) / unit_leaves(n) + 1) / 2;
+}
+constexpr int kMaxWaves = line_waves(kEdtMaxSide);  // 8
+
+// LDS of a block: the padded tile, then the minimisers at the cuts (Index: uint8_t for
+// lines of at most 256 samples, else uint16_t).
+template <class Index>
+constexpr size_t line_lds_bytes(int n) {
+  return (size_t)(n + kPad) * kLines * sizeof(int) +
+         (size_t)(line_leaves(n) + 1) * kLines * sizeof(Index);
+}
+
+__device__ __forceinline__ int min3(int a, int b, int c) { return min(min(a, b), c); }
+__device__ __forceinline__ int key_row(int key) { return (key >> 1) & ((1 << (kShift - 1)) - 1); }
+
+// x, opaque to the optimiser.  Where it is used, this toolchain otherwise folds
+// d * d + q * q behind a select into one v_dot4_u32_u8, which adds the select's condition
+// and drops the bits above the eighth (wrong fields; seen in the assembly), or turns the
+// loop's 32 differences into as many induction variables (95 registers, half again as
+// many instructions).
+__device__ __forceinline__ int opaque(int x) {
+  asm("" : "+v"(x));
+  return x;
+}
+
+// Minima over rows lo .. hi (rows past hi are candidates like any other, at worst padding)
+// of word(q) + (p^2 - 2 p q) << kShift for the kLeaf outputs p from p0 on, less p^2: four
+// rows per round, every row serving all outputs.  word(v, q): the tile word v of row q.
+template <class Word>
+__device__ __forceinline__ void leaf_minima(const int* col, int p0, int lo, int hi,
+                                            int (&acc)[kLeaf], Word&& word) {
 #pragma unroll
-  for (int d = 1; d < kG; ++d) {
-    const int v = __shfl(lm, lane - d);
-    if (start == kNil && band - d >= 0) start = v;
-  }
+  for (int j = 0; j < kLeaf; ++j) acc[j] = 0x7FFFFFFF;
+  const int s0 = p0 << (kShift + 1), s1 = -s0, s2 = -2 * s0, s3 = -3 * s0;
+  for (int q = lo; q <= hi; q += 4) {
+    const int* r = col + q * kLines;
+    const int g0 = r[0], g1 = r[kLines], g2 = r[2 * kLines], g3 = r[3 * kLines];
+    const int v0 = opaque(q << (kShift + 1)), v1 = opaque(v0 + (1 << (kShift + 1))),
+              v2 = opaque(v0 + (2 << (kShift + 1))), v3 = opaque(v0 + (3 << (kShift + 1)));
+    const int m = opaque(__mul24(q, s1));
+    int b0 = word(g0, q) + m, b1 = word(g1, q + 1) + m + s1, b2 = word(g2, q + 2) + m + s2,
+        b3 = word(g3, q + 3) + m + s3;
 #pragma unroll
-  for (int d = 1; d < kG; ++d) {
-    const int v = __shfl(fm, lane + d);
-    if (start == kNil && band + d < kG) start = v;
-  }
-  if (!active) return;
-  const uint64_t occ = band_occupancy(occ_bits, B);
-  if (start == kNil) {
-    for (int p = lo; p < hi; ++p) emit(p, kNone, (occ >> (p - lo)) & 1u);
-    return;
-  }
-  // The winner c and its successor nc (with their F) stay in registers, so an output
-  // whose winner does not change reads no LDS.
-  int c = start, Fc = F(c);
-  int nc = nxt[c * kTs], Fn = nc == kNil ? 0 : F(nc);
-  for (int p = lo; p < hi; ++p) {
-    while (nc != kNil && Fn + p * (p - 2 * nc) <= Fc + p * (p - 2 * c)) {
-      c = nc;
-      Fc = Fn;
-      nc = nxt[c * kTs];
-      if (nc != kNil) Fn = F(nc);
+    for (int j = 0; j < kLeaf; ++j) {
+      acc[j] = min3(min3(acc[j], b0, b1), b2, b3);
+      b0 -= v0;
+      b1 -= v1;
+      b2 -= v2;
+      b3 -= v3;
     }
-    if (p == lo) {
-      bool moved = false;
-      for (;;) {
-        const int pc = prv[c * kTs];
-        if (pc == kNil) break;
-        const int Fp = F(pc);
-        if (Fp + p * (p - 2 * pc) >= Fc + p * (p - 2 * c)) break;
-        c = pc;
-        Fc = Fp;
-        moved = true;
-      }
-      if (moved) {
-        nc = nxt[c * kTs];
-        Fn = nc == kNil ? 0 : F(nc);
-      }
-    }
-    emit(p, (uint32_t)(Fc + p * (p - 2 * c)), (occ >> (p - lo)) & 1u);
   }
 }
 
-// One field of kLines lines, one block (fld 0: D_out, 1: D_in).  A voxel's record
-// after the previous pass holds its occupancy and one value v: the sample of the
-// field it is not a source of (D_out's for a free voxel, D_in's for an occupied one;
-// its own field is 0 there).
-//   1. Stage the samples into the tile (thread t: line t % kLines, q = t / kLines +
-//      (kFhThreads / kLines) k, kBatch loads in flight) and the occupancy into
-//      occ_bits[q] (bit = line).  decode(raw, occ) returns v as a 32-bit value
-//      (kNone: no sample).
-//   2. D_out: FH over the lines that hold a free voxel, written at the free voxels.
-//   3. D_in: at each occupied voxel p a search outward from p: candidates q = p +- d
-//      for d = 1, 2, ... (f_in(q) = 0 on free q, v(q) on occupied q), stopping once d^2
-//      reaches the best value found, which is then exact since every farther q costs
-//      at least d^2.  Obstacles are thin against a line, so the search ends after a
-//      few steps.  The occupied voxels of the tile are listed during staging and
-//      shared out evenly over the block's threads; a tile with more than kInList of
-//      them, or a search that would pass kInReach, is transformed by FH instead.
-// write(p, D) stores the result of the thread's line and write_at(line, p, D) that of
-// line `line` of the block (D = kNone: no source of the field on the line).
-constexpr int kInReach = 64;
-constexpr int kInList = 2048;  // occupied voxels listed per tile, (q << 4) | line
-static_assert(kLines <= 16 && kEdtMaxSide <= 4096, "a list entry fits 16 bits");
+// Transforms the block's lines of n samples: load(q) is the record of row q of the calling
+// lane's line (lanes past the grid repeat its last line: the same values to the same
+// places).  A voxel's record after the previous pass holds its occupancy and one value:
+// the sample of the field it is not a source of.  decode(rec, occ) returns it, at most
+// kFar; emit(p, D, occ) receives D_out of each free voxel and D_in of each occupied one.
+// Every thread of the block calls this.
+template <int kPer, class Index, class Load, class Decode, class Emit>
+__device__ __forceinline__ void transform_lines(int* lds, int n, Load&& load, Decode&& decode,
+                                                Emit&& emit) {
+  const int team = threadIdx.x / kLines, teams = blockDim.x / kLines;
+  const int nleaf = line_leaves(n);
+  constexpr int kRows = kPer * kLeaf;  // rows of a unit
+  const int row0 = team * kRows;
+  int* col = lds + threadIdx.x % kLines;  // row q of this lane's line: col[q * kLines]
+  Index* cut =
+      reinterpret_cast<Index*>(lds + (n + kPad) * kLines) + threadIdx.x % kLines;  // cut[i * kLines]
 
-template <class Val, class Link, class Rec, class Decode, class Write, class WriteAt>
-__device__ __forceinline__ void fh_lines(uint32_t* lds, int n, const Rec* base, long long stride,
-                                         bool stage_ok, bool line_ok, int fld,
-                                         Decode&& decode, Write&& write, WriteAt&& write_at) {
-  constexpr uint32_t kNoVal = Tile<Val, Link>::kNoVal;
-  Tile<Val, Link> T = carve_tile<Val, Link>(lds, n);
-  uint32_t* occ_bits = lds + tile_bytes<Val, Link>(n) / sizeof(uint32_t);  // [n], bit = line
-  // Lines with an output (a voxel that is not a source of the field), voxels listed.
-  uint32_t* flags = occ_bits + n;
-  uint16_t* list = reinterpret_cast<uint16_t*>(flags + 2);  // [kInList]
-  for (int i = threadIdx.x; i < n + 2; i += kFhThreads) occ_bits[i] = 0u;
-  __syncthreads();
-
-  constexpr int kRowsPerPass = kFhThreads / kLines;  // 16
-  constexpr int kBatch = 16;
-  const int sl = threadIdx.x % kLines;
-  const uint32_t sbit = 1u << sl;
+  uint32_t occ_rows = 0u;  // bit kRows - 1 - k: row row0 + k of this lane's line is occupied
   {
-    bool has_output = false;
-    for (int q0 = threadIdx.x / kLines; q0 < n; q0 += kRowsPerPass * kBatch) {
-      Rec v[kBatch];
+    // Rows past the line repeat its last row.
+    decltype(load(0)) v[kRows];
 #pragma unroll
-      for (int j = 0; j < kBatch; ++j) v[j] = base[min(q0 + j * kRowsPerPass, n - 1) * stride];
+    for (int k = 0; k < kRows; ++k) v[k] = load(min(row0 + k, n - 1));
 #pragma unroll
-      for (int j = 0; j < kBatch; ++j) {
-        const int q = q0 + j * kRowsPerPass;
-        if (q < n) {
-          bool occ = false;
-          const uint32_t x = decode(v[j], occ);
-          // D_out's sample is 0 on occupied voxels; D_in keeps v and tells the
-          // sources (free voxels, sample 0) by their occupancy bit.
-          const uint32_t sample = (fld == 0 && occ) ? 0u : x;
-          T.f[q * kTs + sl] = (Val)(stage_ok && sample != kNone ? sample : kNoVal);
-          if (stage_ok && occ) {
-            atomicOr(&occ_bits[q], sbit);
-            if (fld == 1) {
-              const uint32_t at = atomicAdd(&flags[1], 1u);
-              if (at < (uint32_t)kInList) list[at] = (uint16_t)((q << 4) | sl);
-            }
-          }
-          has_output |= stage_ok && (occ == (fld == 1));
+    for (int k = 0; k < kRows; ++k) {
+      const int q = min(row0 + k, n - 1);
+      bool occ = false;
+      const int x = opaque((int)decode(v[k], occ));
+      col[q * kLines] = occ ? ~x : (x + __mul24(q, q)) << kShift;
+      occ_rows = (occ_rows << 1) | (occ ? 1u : 0u);
+    }
+  }
+  auto pad = [&](bool far_in) {  // rows after the line: no source of the field at hand
+#pragma unroll
+    for (int k = 0; k < kPad; ++k)
+      col[(n + k) * kLines] = far_in ? ~kFar : (kFar + (n + k) * (n + k)) << kShift;
+  };
+  if (team == 0) {
+    pad(true);
+    cut[0] = 0;                            // minimisers before the first cut and after the
+    cut[nleaf * kLines] = (Index)(n - 1);  // last one: the ends of the line bound them
+  }
+  // D_in at the occupied voxels: f_in is 0 on free voxels.  D_in(p) is at most f_in(p), and
+  // at most the squared distance to any free row, so only nearby rows matter (obstacles
+  // are thin against a line).
+  if (block_any<kMaxWaves>(occ_rows != 0u)) {
+    for (int i = team; i < nleaf; i += teams) {
+      const int p0 = i * kLeaf;
+      int own[kLeaf], most = -1, least = kFar;  // f_in at the occupied voxels, negative at free ones
+#pragma unroll
+      for (int j = 0; j < kLeaf; ++j) own[j] = ~col[min(p0 + j, n - 1) * kLines];
+#pragma unroll
+      for (int j = 0; j < kLeaf; ++j) {
+        most = max(most, own[j]);
+        least = min(least, own[j]);
+      }
+      if (most < 0) continue;
+      int reach = min((int)sqrtf((float)most) + 1, n);
+      if (least < 0) {
+        reach = min(reach, kLeaf - 1);  // a free row among the outputs
+      } else {
+#pragma unroll
+        for (int d = 16; d >= 4; d -= 4) {  // a free row d from the nearer end?
+          const int w = max(col[max(p0 - d, 0) * kLines], col[min(p0 + kLeaf - 1 + d, n - 1) * kLines]);
+          if (w >= 0) reach = min(reach, d + kLeaf - 1);
         }
       }
-    }
-    if (has_output) atomicOr(&flags[0], sbit);
-  }
-  __syncthreads();
-  const Band B = my_band(n);
-  const uint32_t with_output = flags[0];
-  if (with_output == 0u) return;  // uniform across the block
-  const bool active = line_ok && ((with_output >> B.line) & 1u);
-  if (fld == 0) {
-    tile_fh(T, n, active, occ_bits, [&](int p, uint32_t d, bool o) {
-      if (!o) write(p, d);
-    });
-    return;
-  }
-
-  // D_in by the bounded search, listed voxel i on thread i mod kFhThreads.
-  const uint32_t n_occ = flags[1];
-  bool unresolved = n_occ > (uint32_t)kInList;
-  for (int i = threadIdx.x; !unresolved && i < (int)n_occ; i += kFhThreads) {
-    const int e = list[i];
-    const int line = e & 15, p = e >> 4;
-    const Val* f = T.f + line;
-    const uint32_t fp = f[p * kTs];
-    uint32_t best = fp == kNoVal ? kNone : fp;
-    const int dmax = max(p, n - 1 - p);  // beyond it no candidate is left
-    // kStep distances per round, all loads of a round issued together; after a
-    // round every candidate left costs at least (d0 + kStep)^2.
-    constexpr int kStep = 4;
-    bool done = false;
-    for (int d0 = 1; d0 <= kInReach; d0 += kStep) {
-      uint32_t ob[2 * kStep], fb[2 * kStep];
+      int acc[kLeaf];
+      leaf_minima(col, p0, max(p0 - reach, 0), min(p0 + kLeaf - 1 + reach, n - 1), acc,
+                  [](int w, int q) { return (max(~w, 0) + __mul24(q, q)) << kShift; });
 #pragma unroll
-      for (int c = 0; c < kStep; ++c) {
-        const int qa = max(p - d0 - c, 0), qb = min(p + d0 + c, n - 1);
-        ob[2 * c] = occ_bits[qa];
-        fb[2 * c] = f[qa * kTs];
-        ob[2 * c + 1] = occ_bits[qb];
-        fb[2 * c + 1] = f[qb * kTs];
-      }
-#pragma unroll
-      for (int c = 0; c < 2 * kStep; ++c) {
-        const int d = d0 + c / 2;
-        const int q = (c & 1) ? p + d : p - d;
-        const uint32_t fq = ((ob[c] >> line) & 1u) ? fb[c] : 0u;
-        if (q >= 0 && q < n && fq != kNoVal) best = min(best, (uint32_t)(d * d) + fq);
-      }
-      const int dn = d0 + kStep;  // nearest distance not yet searched
-      if (dn > dmax || (uint32_t)(dn * dn) >= best) {
-        done = true;
-        break;
+      for (int j = 0; j < kLeaf; ++j) {
+        const int p = p0 + j;
+        if (p < n && own[j] >= 0) emit(p, (uint32_t)((acc[j] >> kShift) + p * p), true);
       }
     }
-    if (done)
-      write_at(line, p, best);
-    else
-      unresolved = true;  // the search would pass kInReach
+    __syncthreads();
+    // The occupied voxels become D_out's sources (sample 0), marked by bit 0.
+    for (uint32_t rows = occ_rows; rows != 0u; rows &= rows - 1u) {
+      const int q = min(row0 + kRows - 1 - __builtin_ctz(rows), n - 1);
+      col[q * kLines] = (__mul24(q, q) << kShift) | 1;
+    }
   }
-  if (!__syncthreads_or(unresolved)) return;
-  // FH on f_in: the free voxels' samples become 0 (each thread rewrites the entries
-  // it staged).
-  for (int q = threadIdx.x / kLines; q < n; q += kRowsPerPass)
-    if (!((occ_bits[q] >> sl) & 1u)) T.f[q * kTs + sl] = (Val)0;
+  if (team == 0) pad(false);
   __syncthreads();
-  tile_fh(T, n, active, occ_bits, [&](int p, uint32_t d, bool o) {
-    if (o) write(p, d);
-  });
+
+  // The minimiser at the unit's first output, over the whole line (the first unit's is
+  // bounded by row 0 instead), eight reads in flight.
+  if (row0 > 0 && row0 < n) {
+    int best = 0x7FFFFFFF, t = 0;  // t = (p^2 - 2 p q) << kShift | 2 q, less the p^2 term
+    const int dt = 2 - (row0 << (kShift + 1));
+    int q = 0;
+    for (; q + 8 <= n; q += 8) {
+      const int* r = col + q * kLines;
+      int g[8];
+#pragma unroll
+      for (int c = 0; c < 8; ++c) g[c] = r[c * kLines];
+#pragma unroll
+      for (int c = 0; c < 8; c += 2)
+        best = min3(best, g[c] + (t + c * dt), g[c + 1] + (t + (c + 1) * dt));
+      t += 8 * dt;
+    }
+    for (; q < n; ++q, t += dt) best = min(best, col[q * kLines] + t);
+    cut[team * kPer * kLines] = (Index)key_row(best);
+  }
+  __syncthreads();
+
+  // The other cuts, by halving, each between its neighbours' minimisers.
+#pragma unroll
+  for (int s = kPer / 2; s >= 1; s >>= 1) {
+    for (int i = (2 * team + 1) * s; i < nleaf; i += 2 * teams * s) {
+      const int lo = cut[(i - s) * kLines], hi = cut[min(i + s, nleaf) * kLines];
+      int key = 0x7FFFFFFF;
+      const int s1 = 2 - ((i * kLeaf) << (kShift + 1)), s2 = 2 * s1, s3 = 3 * s1;
+      for (int q = lo; q <= hi; q += 4) {
+        const int* r = col + q * kLines;
+        const int m = __mul24(q, s1);
+        key = min3(key, r[0] + m, r[kLines] + m + s1);
+        key = min3(key, r[2 * kLines] + m + s2, r[3 * kLines] + m + s3);
+      }
+      cut[i * kLines] = (Index)min(key_row(key), hi);
+    }
+    __syncthreads();
+  }
+
+  for (int i = team; i < nleaf; i += teams) {
+    const int p0 = i * kLeaf;
+    int acc[kLeaf];
+    leaf_minima(col, p0, cut[i * kLines], cut[(i + 1) * kLines], acc,
+                [](int w, int) { return w; });
+    int own[kLeaf];
+#pragma unroll
+    for (int j = 0; j < kLeaf; ++j) own[j] = col[min(p0 + j, n - 1) * kLines];
+#pragma unroll
+    for (int j = 0; j < kLeaf; ++j) {
+      const int p = p0 + j;
+      if (p < n && !(own[j] & 1))
+        emit(p, (uint32_t)(acc[j] + (__mul24(p, p) << kShift)) >> kShift, false);
+    }
+  }
 }
 
-// Work item (tile, field) of block b.  All D_out items come first (they take longest,
-// so the short D_in blocks fill the end of the launch).  Within a field, blocks are
-// dispatched to XCD b mod 8; the G neighbouring tiles that share 128-byte lines of the
-// records form a group that runs on one XCD, so each line is fetched into one L2 once,
-// and consecutive groups go to consecutive XCDs, so that every XCD gets a share of
-// every region of the grid (a contiguous run per XCD leaves the XCDs holding the
-// obstacle-dense regions to finish last).  Returns false for the padding blocks.
+// Block b's tile.  Blocks are dispatched to XCD b mod 8; the G neighbouring tiles that
+// share 128-byte lines of the records form a group that runs on one XCD, so each line is
+// fetched into one L2 once, and consecutive groups go to consecutive XCDs, so that every
+// XCD gets a share of every region of the grid.  Tiles past the last are padding.
 template <int G>
-__host__ __device__ __forceinline__ long long xcd_half(long long tiles) {
-  return 8 * (((tiles + G - 1) / G + 7) / 8) * G;  // blocks per field, a multiple of 8
+__host__ __device__ __forceinline__ long long xcd_blocks(long long tiles) {
+  return 8 * (((tiles + G - 1) / G + 7) / 8) * G;
 }
 template <int G>
-__device__ __forceinline__ bool xcd_item(long long tiles, long long& tile, int& fld) {
-  const long long half = xcd_half<G>(tiles);
-  fld = blockIdx.x >= half;
-  const long long b = blockIdx.x - (fld ? half : 0);
-  const long long k = b / 8;  // k-th item of this XCD
-  tile = ((b % 8) + 8 * (k / G)) * G + k % G;
-  return tile < tiles;
+__device__ __forceinline__ uint32_t xcd_tile() {
+  const uint32_t b = blockIdx.x, k = b / 8;  // k-th tile of this XCD
+  return ((b % 8) + 8 * (k / G)) * G + k % G;
 }
-template <int G>
-unsigned xcd_grid(long long tiles) {
-  return (unsigned)(2 * xcd_half<G>(tiles));
-}
-// Tiles per 128-byte line: 16 lines x 2-byte x-records, 16 lines x 4-byte y-records.
-constexpr int kGroupY = 4, kGroupZ = 2;
+// Tiles per 128-byte line: 32 lines x 2-byte x-records, 32 lines x 4-byte y-records.
+constexpr int kGroupY = 2, kGroupZ = 1;
 
-// Pass y: block = 16 consecutive lines (x, z) of one field.
-template <class Val, class Link>
-__global__ __launch_bounds__(kFhThreads) void edt_pass_y_kernel(
+// The element `off` bytes after a uniform base (off < 2^32).
+template <class T>
+__device__ __forceinline__ T& at_byte(T* base, uint32_t off) {
+  return *reinterpret_cast<T*>(reinterpret_cast<char*>(base) + off);
+}
+template <class T>
+__device__ __forceinline__ const T& at_byte(const T* base, uint32_t off) {
+  return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + off);
+}
+
+// Pass y: block = 32 consecutive lines (z, x).
+template <int kPer, class Index>
+__global__ __launch_bounds__(64 * kMaxWaves) void edt_pass_y_kernel(
     const uint16_t* __restrict__ xrec, uint32_t* __restrict__ yrec, int nx, int ny, int nz) {
-  extern __shared__ uint32_t lds[];
-  const int lines = nx * nz;
-  long long tile;
-  int fld;
-  if (!xcd_item<kGroupY>((lines + kLines - 1) / kLines, tile, fld)) return;  // whole block
-  const int line0 = (int)tile * kLines;  // flattened (z, x) < 2^18
-  const long long plane = (long long)nx * ny;
-  auto line_out = [&](int l) {  // records of block line l (clamped into the grid)
-    const int i = min(line0 + l, lines - 1);
-    const int z = i / nx;
-    return yrec + z * plane + (i - z * nx);
-  };
-  const int si = line0 + (int)(threadIdx.x % kLines);
-  const bool stage_ok = si < lines;
-  const int sz = stage_ok ? si / nx : 0, sx = stage_ok ? si - sz * nx : 0;
-  const int line = (int)(threadIdx.x / kG);
-  uint32_t* out = line_out(line);
-  const uint32_t occ_flag = fld == 1 ? kYOcc : 0u;
-  fh_lines<Val, Link>(
-      lds, ny, xrec + sz * plane + sx, nx, stage_ok, line0 + line < lines, fld,
+  extern __shared__ int lds[];
+  const uint32_t lines = (uint32_t)nx * nz, tile = xcd_tile<kGroupY>();
+  if (tile * kLines >= lines) return;  // whole block
+  const uint32_t l = min(tile * kLines + threadIdx.x % kLines, lines - 1u);
+  const uint32_t z = l / (uint32_t)nx, x = l - z * nx;
+  const uint32_t at = z * (uint32_t)(nx * ny) + x;  // the line's first voxel, < 2^27
+  transform_lines<kPer, Index>(
+      lds, ny, [&](int q) { return at_byte(xrec, 2u * at + __umul24(q, 2 * nx)); },
       [](uint16_t r, bool& occ) -> uint32_t {
         occ = r & kXOcc;
-        if (r & kXNone) return kNone;
-        const uint32_t d = r & 0x3FFFu;
-        return d * d;
+        const uint32_t d = r & 0x7FFFu;
+        return __umul24(d, d);
       },
-      [&](int p, uint32_t d) { out[(long long)p * nx] = occ_flag | (d == kNone ? kYNone : d); },
-      [&](int l, int p, uint32_t d) {
-        line_out(l)[(long long)p * nx] = occ_flag | (d == kNone ? kYNone : d);
+      [&](int p, uint32_t d, bool occ) {
+        at_byte(yrec, 4u * at + __umul24(p, 4 * nx)) = d | (occ ? kYOcc : 0u);
       });
 }
 
@@ -636,72 +507,69 @@ __global__ __launch_bounds__(kFhThreads) void edt_pass_y_kernel(
 struct FieldOut {
   float* phi;     // [nvox] or null
   uint32_t* d2;   // [2][nvox] or null
-  long long nvox;
+  uint32_t nvox;
   double voxel;
   uint32_t none_value;
-  __device__ __forceinline__ void put(long long i, bool occ, uint32_t d) const {
-    const uint32_t D = d == kNone ? none_value : d;
+  // off: four times the voxel's index.
+  __device__ __forceinline__ void put(uint32_t off, bool occ, uint32_t d) const {
+    const uint32_t D = d >= kNoneD ? none_value : d;
     if (d2) {
-      d2[i] = occ ? 0u : D;
-      d2[nvox + i] = occ ? D : 0u;
+      at_byte(d2, off) = occ ? 0u : D;
+      at_byte(d2 + nvox, off) = occ ? D : 0u;
     }
     if (phi) {
       const double v = voxel * __builtin_sqrt((double)D);
-      phi[i] = (float)(occ ? -v : v);
+      at_byte(phi, off) = (float)(occ ? -v : v);
     }
   }
 };
 
-// Pass z: block = 16 consecutive lines (x, y) of one field; the D_out block writes the
-// outputs of the free voxels, the D_in block those of the occupied ones.
-template <class Link>
-__global__ __launch_bounds__(kFhThreads) void edt_pass_z_kernel(
+// Pass z: block = 32 consecutive lines (y, x); writes the outputs.
+template <int kPer, class Index>
+__global__ __launch_bounds__(64 * kMaxWaves) void edt_pass_z_kernel(
     const uint32_t* __restrict__ yrec, int nx, int ny, int nz, FieldOut fo) {
-  extern __shared__ uint32_t lds[];
-  const long long plane = (long long)nx * ny;
-  long long tile;
-  int fld;
-  if (!xcd_item<kGroupZ>((plane + kLines - 1) / kLines, tile, fld)) return;  // whole block
-  const long long line0 = tile * kLines;  // flattened (y, x)
-  const long long si = line0 + (long long)(threadIdx.x % kLines);
-  const long long li = line0 + (long long)(threadIdx.x / kG);
-  const long long out0 = li < plane ? li : 0;
-  const bool occ = fld == 1;
-  fh_lines<uint32_t, Link>(
-      lds, nz, yrec + (si < plane ? si : 0), plane, si < plane, li < plane, fld,
-      [](uint32_t r, bool& o) -> uint32_t {
-        o = r & kYOcc;
-        return (r & kYNone) ? kNone : (r & kYVal);
+  extern __shared__ int lds[];
+  const uint32_t plane = (uint32_t)nx * ny, tile = xcd_tile<kGroupZ>();
+  if (tile * kLines >= plane) return;  // whole block
+  const uint32_t at = min(tile * kLines + threadIdx.x % kLines, plane - 1u);
+  transform_lines<kPer, Index>(
+      lds, nz, [&](int q) { return at_byte(yrec, 4u * (at + __umul24(q, plane))); },
+      [](uint32_t r, bool& occ) -> uint32_t {
+        occ = r & kYOcc;
+        return r & ~kYOcc;
       },
-      [&](int p, uint32_t d) { fo.put(out0 + p * plane, occ, d); },
-      [&](int l, int p, uint32_t d) {
-        const long long i = line0 + l < plane ? line0 + l : plane - 1;
-        fo.put(i + p * plane, occ, d);
-      });
+      [&](int p, uint32_t d, bool occ) { fo.put(4u * (at + __umul24(p, plane)), occ, d); });
 }
 
-template <class Val, class Link>
-size_t fh_lds_bytes(int n) {
-  return tile_bytes<Val, Link>(n) + (size_t)(n + 2) * sizeof(uint32_t) +
-         (size_t)kInList * sizeof(uint16_t);
+template <int kPer, class Index>
+void launch_pass_y(const uint16_t* xrec, uint32_t* yrec, int nx, int ny, int nz,
+                   hipStream_t stream) {
+  const long long tiles = ((long long)nx * nz + kLines - 1) / kLines;
+  hipLaunchKernelGGL((edt_pass_y_kernel<kPer, Index>), dim3((unsigned)xcd_blocks<kGroupY>(tiles)),
+                     dim3(64 * line_waves(ny)), line_lds_bytes<Index>(ny), stream, xrec, yrec, nx,
+                     ny, nz);
+}
+template <int kPer, class Index>
+void launch_pass_z(const uint32_t* yrec, int nx, int ny, int nz, const FieldOut& fo,
+                   hipStream_t stream) {
+  const long long tiles = ((long long)nx * ny + kLines - 1) / kLines;
+  hipLaunchKernelGGL((edt_pass_z_kernel<kPer, Index>), dim3((unsigned)xcd_blocks<kGroupZ>(tiles)),
+                     dim3(64 * line_waves(nz)), line_lds_bytes<Index>(nz), stream, yrec, nx, ny,
+                     nz, fo);
 }
 
-template <class Link>
-void launch_fh_passes(const uint16_t* xrec, uint32_t* yrec, int nx, int ny, int nz,
-                      const FieldOut& fo, hipStream_t stream) {
-  const long long plane = (long long)nx * ny;
-  const long long ly = (long long)nx * nz;
-  const dim3 ygrid(xcd_grid<kGroupY>((ly + kLines - 1) / kLines));
-  // x-pass distances are at most nx - 1: their squares fit 16 bits below 0xFFFF
-  // when nx <= 256.
-  if (nx <= 256)
-    edt_pass_y_kernel<uint16_t, Link><<<ygrid, kFhThreads, fh_lds_bytes<uint16_t, Link>(ny),
-                                        stream>>>(xrec, yrec, nx, ny, nz);
-  else
-    edt_pass_y_kernel<uint32_t, Link><<<ygrid, kFhThreads, fh_lds_bytes<uint32_t, Link>(ny),
-                                        stream>>>(xrec, yrec, nx, ny, nz);
-  edt_pass_z_kernel<Link><<<dim3(xcd_grid<kGroupZ>((plane + kLines - 1) / kLines)), kFhThreads,
-                            fh_lds_bytes<uint32_t, Link>(nz), stream>>>(yrec, nx, ny, nz, fo);
+void launch_line_passes(const uint16_t* xrec, uint32_t* yrec, int nx, int ny, int nz,
+                        const FieldOut& fo, hipStream_t stream) {
+  const auto y = ny <= 64    ? launch_pass_y<1, uint8_t>
+                 : ny <= 128 ? launch_pass_y<2, uint8_t>
+                 : ny <= 256 ? launch_pass_y<4, uint8_t>
+                             : launch_pass_y<4, uint16_t>;
+  const auto z = nz <= 64    ? launch_pass_z<1, uint8_t>
+                 : nz <= 128 ? launch_pass_z<2, uint8_t>
+                 : nz <= 256 ? launch_pass_z<4, uint8_t>
+                             : launch_pass_z<4, uint16_t>;
+  y(xrec, yrec, nx, ny, nz, stream);
+  z(yrec, nx, ny, nz, fo, stream);
 }
 
 }  // namespace
@@ -712,8 +580,7 @@ size_t edt_workspace_bytes(long long nvox) {
 }
 
 size_t edt_lds_bytes(int n_line) {
-  return n_line <= 255 ? fh_lds_bytes<uint32_t, uint8_t>(n_line)
-                       : fh_lds_bytes<uint32_t, uint16_t>(n_line);
+  return n_line <= 256 ? line_lds_bytes<uint8_t>(n_line) : line_lds_bytes<uint16_t>(n_line);
 }
 
 int launch_edt(const uint8_t* occ, int nx, int ny, int nz, float voxel, float* phi,
@@ -738,11 +605,8 @@ int launch_edt(const uint8_t* occ, int nx, int ny, int nz, float voxel, float* p
   else
     hipLaunchKernelGGL(edt_pass_x_kernel<kEdtMaxSide / 64>, xgrid, dim3(64 * kRowWaves), 0,
                        stream, occ, nx, rows, xrec);
-  const FieldOut fo{phi, d2, nvox, (double)voxel, none_value};
-  if (ny <= 255 && nz <= 255)
-    launch_fh_passes<uint8_t>(xrec, yrec, nx, ny, nz, fo, stream);
-  else
-    launch_fh_passes<uint16_t>(xrec, yrec, nx, ny, nz, fo, stream);
+  const FieldOut fo{phi, d2, (uint32_t)nvox, (double)voxel, none_value};
+  launch_line_passes(xrec, yrec, nx, ny, nz, fo, stream);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
