@@ -24,8 +24,7 @@ constexpr int kWeightsPerBlock = 1024;        // weights_out elements per K2 blo
 // arrive in a few wide scalar loads.
 struct alignas(16) LinkPair {
   uint32_t mask;
-  float bthr;                  // (R_la + R_lb)^2 of the link bounding spheres
-  uint32_t pad_[2];
+  uint32_t pad_[3];
   float sthr[kSpl];            // (r_i + R_lb)^2: sphere i of la vs lb's bound
   float rr2[kSpl * kSpl];      // (r_i + r_j)^2 per pair (0 if not a pair)
   float rs[kSpl * kSpl];       // r_i + r_j
@@ -40,6 +39,8 @@ struct DevRobot {
   uint32_t slot_active;        // bit s set when slot s holds a sphere
   uint32_t pad0_[3];
   // Self-collision pairs grouped by link pair, index la * kNdof + lb.
+  float bthr[kNdof * kNdof];   // (R_la + R_lb)^2 of the link bounding spheres (0: no pair)
+  uint32_t pad1_[3];
   LinkPair lp[kNdof * kNdof];
   float lbound[kNdof];         // bounding radius of each link's spheres about its slot-0 sphere
   int32_t n_pairs;             // distinct pairs after de-duplication

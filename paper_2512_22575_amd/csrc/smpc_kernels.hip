@@ -405,10 +405,13 @@ __device__ __forceinline__ float coarse_bound(__amdgpu_buffer_rsrc_t crsrc, cons
 
 // Forward kinematics (eq. 6) of q0 + dq with sin/cos of q0 + dq by angle addition,
 // so the large common angle q0 enters exactly once and only the small dq is
-// rounded; writes the sphere slot centres and returns the end-effector frame.
+// rounded; writes the sphere slot centres, calls placed(i) once link i's are there, and
+// returns the end-effector frame.
+template <class Placed>
 __device__ __forceinline__ Frame fk_spheres(const DevRobot* __restrict__ rob, const float* sc0,
                                             const float (&dq)[kNdof], float (&px)[kSlots],
-                                            float (&py)[kSlots], float (&pz)[kSlots]) {
+                                            float (&py)[kSlots], float (&pz)[kSlots],
+                                            Placed&& placed) {
   Frame T = identity_frame();
 #pragma unroll
   for (int i = 0; i < kNdof; ++i) {
@@ -423,6 +426,7 @@ __device__ __forceinline__ Frame fk_spheres(const DevRobot* __restrict__ rob, co
       const int s = i * kSpl + j;
       transform_point(T, rob->sc[s][0], rob->sc[s][1], rob->sc[s][2], px[s], py[s], pz[s]);
     }
+    placed(i);
   }
   return T;
 }
@@ -445,6 +449,9 @@ __device__ __forceinline__ float state_limit_cost(const StepParams& p, const flo
   }
   return fmaf(p.w_q, c_q, fmaf(p.w_qd, c_qd, p.w_ns * c_ns));
 }
+
+// Whether x holds in any active lane of the wave (a scalar condition).
+__device__ __forceinline__ bool any_lane(bool x) { return __builtin_amdgcn_ballot_w64(x) != 0ull; }
 
 // Cost charged by thread (m, k): control terms of u_k and state terms of state k+1.
 //   q0 : start positions (wave-uniform);  dq, qd : q_{k+1} - q0 and qd_{k+1};  u : u_k;
@@ -471,48 +478,72 @@ __device__ __forceinline__ float step_cost(const DevRobot* __restrict__ rob, con
   float cost = fmaf(p.w_smooth, c_u2, p.w_qdd * c_ulim);
   if (!terminal) cost += state_limit_cost(p, q0, dq, qd);
 
+  // Environment collision (eqs. 17, 19, 20): with coarse bounds, a sphere first fetches the
+  // bound of its lookup cell; a sphere whose bound clears its threshold has phi >=
+  // threshold, i.e. a hinge of exactly 0, and needs no trilinear lookup.  A link's bounds
+  // are fetched as soon as its spheres are placed and tested two links later, so that the
+  // 28 gathers run beside the kinematics and few results wait in registers (issued
+  // together after the pose term, they held 28 registers through the self-collision
+  // tests, and a full chip's address units worked at them alone: K = 4096, H = 40 on a new
+  // 200^3 map 27.1 us per period, 25.8 now).
   float px[kSlots], py[kSlots], pz[kSlots];
-  const Frame T = fk_spheres(rob, sc0, dq, px, py, pz);
+  float bound[kSlots];
+  uint32_t need = rob->slot_active;  // bit s: sphere s needs its lookup
+  auto test_bounds = [&](int l) {
+#pragma unroll
+    for (int s = l * kSpl; s < (l + 1) * kSpl; ++s)
+      if (bound[s] >= p.env_thr[s]) need &= ~(1u << s);
+  };
+  const bool bounded = p.coarse_bytes != 0u;
+  const Frame T = fk_spheres(rob, sc0, dq, px, py, pz, [&](int l) {
+    if (!bounded) return;
+#pragma unroll
+    for (int s = l * kSpl; s < (l + 1) * kSpl; ++s)
+      bound[s] = coarse_bound(crsrc, p, px[s], py[s], pz[s]);
+    if (l >= 2) test_bounds(l - 2);
+  });
+  if (bounded) test_bounds(kNdof - 2);
   // Pose tracking (eq. 16) or terminal (eq. 25) cost.
   cost += pose_cost(T, p, terminal ? p.w_term_t : p.w_pose_t, terminal ? p.w_term_r : p.w_pose_r);
 
   if (terminal) return cost;
-
-  // Environment collision (eqs. 17, 19, 20), with the self-collision terms evaluated
-  // while the coarse bounds are in flight.  With coarse bounds, all spheres first
-  // fetch the bound of their lookup cell (one load each, issued together); a sphere
-  // whose bound clears its threshold has phi >= threshold, i.e. a hinge of exactly 0,
-  // and skips the trilinear lookup.
-  const uint32_t active = rob->slot_active;
-  uint32_t need = active;
-  float bound[kSlots];
-  if (p.coarse_bytes != 0u) {
-#pragma unroll
-    for (int s = 0; s < kSlots; ++s) bound[s] = coarse_bound(crsrc, p, px[s], py[s], pz[s]);
-  }
+  if (bounded) test_bounds(kNdof - 1);
 
   // Self collision (eqs. 18-20), grouped by link pair.  When no lane's link bounding
   // spheres overlap, no pair of the two links can overlap and the group is skipped
   // (its hinges are exactly 0); otherwise each sphere of the first link is tested
   // against the second link's bounding sphere the same way, and each remaining pair
-  // takes a squared-distance test, with a square root only on overlap.
+  // takes a squared-distance test, with a square root only on overlap.  All conditions
+  // are per wave (any lane): the tests of the 15 (28) link pairs run back to back and a
+  // group's code has no divergent branch, so a wave alone on its SIMD is not held by a
+  // chain of scalar loads and execution-mask updates (9,200 cycles of such a wave before,
+  // 5,600 now; a lane that a test does not concern adds exactly 0).  Thresholds of absent groups,
+  // spheres and pairs are 0: no squared distance is below.
   float c_self = 0.f;
+  uint32_t near = 0u;  // bit g: link pair g (in the order of the loops) is near in some lane
+  {
+    int g = 0;
 #pragma unroll
-  for (int la = 0; la < kNdof; ++la) {
+    for (int la = 0; la < kNdof; ++la) {
 #pragma unroll
-    for (int lb = kFar ? la + 2 : la; lb < kNdof; ++lb) {
-      const LinkPair& G = rob->lp[la * kNdof + lb];
-      const uint32_t mask = G.mask;
-      if (mask == 0u) continue;
-      bool near = true;
-      if (la != lb) {
+      for (int lb = kFar ? la + 2 : la; lb < kNdof; ++lb, ++g) {
         // A link's bounding sphere is centred on the sphere in its first slot.
         const int ca = la * kSpl, cb = lb * kSpl;
         const float dx = px[ca] - px[cb], dy = py[ca] - py[cb], dz = pz[ca] - pz[cb];
-        near = fmaf(dx, dx, fmaf(dy, dy, dz * dz)) < G.bthr;
+        const bool nr = fmaf(dx, dx, fmaf(dy, dy, dz * dz)) < rob->bthr[la * kNdof + lb];
+        near |= any_lane(nr) ? 1u << g : 0u;
       }
-      if (near) {
+    }
+  }
+  {
+    int g = 0;
+#pragma unroll
+    for (int la = 0; la < kNdof; ++la) {
+#pragma unroll
+      for (int lb = kFar ? la + 2 : la; lb < kNdof; ++lb, ++g) {
+        if (!(near & (1u << g))) continue;
         // The group's constants, fetched together before any of them is used.
+        const LinkPair& G = rob->lp[la * kNdof + lb];
         float sthr[kSpl], rr2[kSpl * kSpl], rs[kSpl * kSpl];
 #pragma unroll
         for (int i = 0; i < kSpl; ++i) sthr[i] = G.sthr[i];
@@ -521,36 +552,37 @@ __device__ __forceinline__ float step_cost(const DevRobot* __restrict__ rob, con
           rr2[b] = G.rr2[b];
           rs[b] = G.rs[b];
         }
+        bool hit[kSpl];
 #pragma unroll
         for (int i = 0; i < kSpl; ++i) {
-          if (!(mask & (0xFu << (i * kSpl)))) continue;
           // Sphere i of la against lb's bounding sphere: when clear, so is each of
           // its pairs with lb (exactly, by the same margin as the link test).
-          if (la != lb) {
-            const int sa = la * kSpl + i, cb = lb * kSpl;
-            const float dx = px[sa] - px[cb], dy = py[sa] - py[cb], dz = pz[sa] - pz[cb];
-            if (!(fmaf(dx, dx, fmaf(dy, dy, dz * dz)) < sthr[i])) continue;
+          const int sa = la * kSpl + i, cb = lb * kSpl;
+          const float dx = px[sa] - px[cb], dy = py[sa] - py[cb], dz = pz[sa] - pz[cb];
+          hit[i] = any_lane(fmaf(dx, dx, fmaf(dy, dy, dz * dz)) < sthr[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < kSpl; ++i) {
+          if (!hit[i]) continue;
+          float d2[kSpl];
+          bool over = false;
+#pragma unroll
+          for (int j = 0; j < kSpl; ++j) {
+            const int sa = la * kSpl + i, sb = lb * kSpl + j;
+            const float dx = px[sa] - px[sb], dy = py[sa] - py[sb], dz = pz[sa] - pz[sb];
+            d2[j] = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+            over |= d2[j] < rr2[i * kSpl + j];
           }
+          if (!any_lane(over)) continue;
 #pragma unroll
           for (int j = 0; j < kSpl; ++j) {
             const int bit = i * kSpl + j;
-            if (!(mask & (1u << bit))) continue;
-            const int sa = la * kSpl + i, sb = lb * kSpl + j;
-            const float dx = px[sa] - px[sb], dy = py[sa] - py[sb], dz = pz[sa] - pz[sb];
-            const float d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-            if (d2 < rr2[bit]) {
-              const float h = rs[bit] - sqrt_hw(d2);
-              c_self = fmaf(h, h, c_self);
-            }
+            const float h = d2[j] < rr2[bit] ? rs[bit] - sqrt_hw(d2[j]) : 0.f;
+            c_self = fmaf(h, h, c_self);
           }
         }
       }
     }
-  }
-  if (p.coarse_bytes != 0u) {
-#pragma unroll
-    for (int s = 0; s < kSlots; ++s)
-      if (bound[s] >= p.env_thr[s]) need &= ~(1u << s);
   }
   float c_env = 0.f;
 #pragma unroll

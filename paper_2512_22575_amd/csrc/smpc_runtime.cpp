@@ -458,7 +458,7 @@ smpc_status smpc_set_robot(smpc_ctx* ctx, const smpc_robot_desc* d) {
     r.lp[lp].rr2[bit] = (float)(rs * rs);
     r.lp[lp].rs[bit] = (float)rs;
     const double bt = bound_r[la] + bound_r[lb];
-    r.lp[lp].bthr = (float)(bt * bt);
+    r.bthr[lp] = (float)(bt * bt);
     const double sb = ctx->slot_radius[a] + bound_r[lb];
     r.lp[lp].sthr[a % kSpl] = (float)(sb * sb);
   }
