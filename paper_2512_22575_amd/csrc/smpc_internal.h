@@ -18,6 +18,10 @@ constexpr int kK1Threads = 256;               // rollout-cost block size (4 wave
 constexpr int kK2Threads = 256;               // reduce/update block size
 constexpr int kOutPerBlock = 8;               // U* outputs merged per K2 block
 constexpr int kWeightsPerBlock = 1024;        // weights_out elements per K2 block
+constexpr int kFoldRows = 64;                 // block partials folded into one
+constexpr int kFoldShift = 6;
+static_assert((1 << kFoldShift) == kFoldRows, "fold width");
+constexpr int kMaxMerged = 1024;              // partials the merge reads without folding
 
 // Self-collision constants of one link pair (la <= lb): bit i * kSpl + j of mask marks
 // the pair (slot la*kSpl+i, slot lb*kSpl+j).  One record, so that a group's constants
@@ -76,6 +80,7 @@ struct StepParams {
   float cmax[3];               // ncx - 1, ncy - 1, ncz - 1
   float cstride[2];            // ncx, ncx * ncy (cell index strides)
   int32_t K, H, R, P;          // samples, horizon, rollouts per K1 block, K1 blocks
+  int32_t Pm, m_shift;         // partials the merge reads: row b of Pm at b << m_shift
   float dt;
   float k_lambda;              // log2(e) / lambda (softmax factors by exp2)
   uint32_t seed_lo, seed_hi;   // sampling mode: Philox key
@@ -116,6 +121,7 @@ struct Request {
   Workspace ws;
   int32_t k1_begin;            // first rollout-cost block of this request in a batch
   int32_t k2_begin;            // first merge block of this request in a batch
+  int32_t kf_begin;            // first fold block of this request in a batch
   int32_t shift_out;           // 1: U_out = [u*_1 .. u*_{H-1}, 0] (receding horizon)
   int32_t c0_in_ws;            // 1: an extra rollout-launch block leaves c0 in ws.c0
 };
@@ -126,6 +132,7 @@ struct LaunchConfig {
   int P;            // number of K1 blocks
   size_t k1_lds;    // dynamic LDS bytes of K1
   int k2_blocks;    // K2 grid
+  int fold_blocks;  // blocks that fold kFoldRows partials each before the merge (0: none)
   bool far_pairs = false;  // every self-collision pair joins links two or more apart
 };
 
@@ -166,18 +173,18 @@ int launch_plan_step_bounds(const DevRobot* robot, const Request& q, const Launc
                             const float* ball_c, float ball_r2, float* out, void* stream,
                             void* events);
 
-// A batch of requests (device array `reqs`; block maps k1_map [k1_blocks] and k2_map
-// [k2_blocks] give each block's request index) as one HIP graph (descriptor upload,
-// both batch kernels, result download),
-// created at the first launch and re-parameterised for every later one.  `*graph` is
+// A batch of requests (device array `reqs`; block maps k1_map [k1_blocks], k2_map
+// [k2_blocks] and kf_map [kf_blocks] give each block's request index) as one HIP graph
+// (descriptor upload, the batch kernels -- the fold among them when `fold`, whether or not
+// this batch has fold blocks -- result download), created at the first launch and re-parameterised for every later one.  `*graph` is
 // the slot's handle (null before the first launch); the caller relaunches it only after
 // the previous launch has completed (a launch for a robot of the other pair kind, `far`,
-// rebuilds the graph).  up: host -> device bytes (descriptors and maps);
+// or the other `fold` rebuilds the graph).  up: host -> device bytes (descriptors and maps);
 // res: device -> host result bytes.  Returns a hipError_t value.
 int launch_batch_graph(void** graph, const DevRobot* robot, void* d_up, const void* h_up,
                        size_t up_bytes, const Request* reqs, const int32_t* k1_map,
-                       int k1_blocks, const int32_t* k2_map, int k2_blocks, size_t k1_lds,
-                       bool f16, bool far, void* h_res, const void* d_res, size_t res_bytes,
+                       int k1_blocks, const int32_t* k2_map, int k2_blocks, const int32_t* kf_map,
+                       int kf_blocks, size_t k1_lds, bool f16, bool far, bool fold, void* h_res, const void* d_res, size_t res_bytes,
                        void* stream);
 void destroy_batch_graph(void* graph);
 

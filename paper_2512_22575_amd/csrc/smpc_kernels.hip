@@ -1079,23 +1079,24 @@ struct StatRows {
   float z[kStatRows], z2[kStatRows];
 };
 
-__device__ __forceinline__ void stats_load(const Workspace& ws, int P, int lane, StatRows& r) {
+__device__ __forceinline__ void stats_load(const Workspace& ws, int P, int shift, int lane,
+                                           StatRows& r) {
 #pragma unroll
   for (int c = 0; c < kStatRows; ++c) {
-    const int b = min(lane + kWave * c, P - 1);
+    const int b = min(lane + kWave * c, P - 1) << shift;
     r.m[c] = ws.part_m[b];
     r.z[c] = ws.part_Z[b];
     r.z2[c] = ws.part_Z2[b];
   }
 }
 
-__device__ __forceinline__ GlobalStats stats_finish(const Workspace& ws, int P, float k_lambda,
-                                                    int lane, const StatRows& r) {
+__device__ __forceinline__ GlobalStats stats_finish(const Workspace& ws, int P, int shift,
+                                                    float k_lambda, int lane, const StatRows& r) {
   double mn = __builtin_inf();
 #pragma unroll
   for (int c = 0; c < kStatRows; ++c)
     if (lane + kWave * c < P) mn = fmin(mn, r.m[c]);
-  for (int b = lane + kWave * kStatRows; b < P; b += kWave) mn = fmin(mn, ws.part_m[b]);
+  for (int b = lane + kWave * kStatRows; b < P; b += kWave) mn = fmin(mn, ws.part_m[b << shift]);
   mn = wave_min_f64(mn);
   float Z = 0.f, Z2 = 0.f;
   if (isfinite(mn)) {
@@ -1107,21 +1108,80 @@ __device__ __forceinline__ GlobalStats stats_finish(const Workspace& ws, int P, 
       Z2 = fmaf(r.z2[c], e * e, Z2);
     }
     for (int b = lane + kWave * kStatRows; b < P; b += kWave) {
-      const double mb = ws.part_m[b];
+      const double mb = ws.part_m[b << shift];
       if (!isfinite(mb)) continue;
       const float e = softmax_factor((float)(mb - mn), k_lambda);
-      Z = fmaf(ws.part_Z[b], e, Z);
-      Z2 = fmaf(ws.part_Z2[b], e * e, Z2);
+      Z = fmaf(ws.part_Z[b << shift], e, Z);
+      Z2 = fmaf(ws.part_Z2[b << shift], e * e, Z2);
     }
   }
   return {mn, wave_sum_f32(Z), wave_sum_f32(Z2)};
 }
 
-__device__ __forceinline__ GlobalStats wave_stats(const Workspace& ws, int P, float k_lambda,
-                                                  int lane) {
+__device__ __forceinline__ GlobalStats wave_stats(const Workspace& ws, int P, int shift,
+                                                  float k_lambda, int lane) {
   StatRows r;
-  stats_load(ws, P, lane, r);
-  return stats_finish(ws, P, k_lambda, lane, r);
+  stats_load(ws, P, shift, lane, r);
+  return stats_finish(ws, P, shift, k_lambda, lane, r);
+}
+
+// Folds kFoldRows block partials into one, in place: rows fb kFoldRows + i, i < kFoldRows, of
+// every array into row fb kFoldRows, as the merge folds them (eqs. 29-30 regrouped).  Used
+// above kMaxMerged partials (K = 4096 at H = 64), because every wave of every merge block
+// reads all the partials it merges: the merge of the 16,384 partials of K = 65536, H = 64
+// took 190 us, beside 300 us of rollouts; folding them (29 MB of N, read once) and merging
+// the 256 that are left takes 9.9 + 6.2 us.  One block per row: every wave folds the
+// statistics of the 64 rows itself (lane = row), then takes every fourth output chunk, its
+// 64 rows in eight loads of 256 contiguous bytes.
+__device__ __forceinline__ void fold_block(const Request& q, int fb) {
+  const StepParams& p = q.p;
+  const Workspace& ws = q.ws;
+  __shared__ float factor[kK2Threads / kWave][kFoldRows];  // < 0: no finite cost in the row
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  const int r0 = fb * kFoldRows, n = min(kFoldRows, p.P - r0);
+  static_assert(kFoldRows == kWave, "one lane per row");
+  const int row = r0 + min(lane, n - 1);
+  const double m = lane < n ? ws.part_m[row] : __builtin_inf();
+  const float z = ws.part_Z[row], z2 = ws.part_Z2[row];
+  const double mn = wave_min_f64(isfinite(m) ? m : __builtin_inf());
+  const float c = isfinite(m) ? softmax_factor((float)(m - mn), p.k_lambda) : -1.f;
+  const float Z = wave_sum_f32(c > 0.f ? z * c : 0.f), Z2 = wave_sum_f32(c > 0.f ? z2 * (c * c) : 0.f);
+  factor[wave][lane] = c;
+  __syncthreads();  // every wave has read row r0
+  if (threadIdx.x == 0) {
+    ws.part_m[r0] = mn;
+    ws.part_Z[r0] = Z;
+    ws.part_Z2[r0] = Z2;
+  }
+  const int n_chunks = (p.H * kNdof + kOutPerBlock - 1) / kOutPerBlock;
+  constexpr int kRowsPerLoad = kWave / kOutPerBlock, kLoads = kFoldRows / kRowsPerLoad;
+  const int g = lane / kOutPerBlock;
+  float f[kLoads];
+#pragma unroll
+  for (int i = 0; i < kLoads; ++i) f[i] = factor[wave][g + kRowsPerLoad * i];
+  for (int ch = wave; ch < n_chunks; ch += kK2Threads / kWave) {
+    float* base = ws.part_N + ((size_t)ch * p.P + r0) * kOutPerBlock + lane % kOutPerBlock;
+    float v[kLoads], acc = 0.f;
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) v[i] = base[min(g + kRowsPerLoad * i, n - 1) * kOutPerBlock];
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i)
+      if (f[i] >= 0.f) acc = fmaf(v[i], f[i], acc);
+#pragma unroll
+    for (int off = kOutPerBlock; off < kWave; off <<= 1) acc += __shfl_xor(acc, off, kWave);
+    if (g == 0) base[0] = acc;
+  }
+}
+
+__global__ __launch_bounds__(kK2Threads) void fold_kernel(const Request q) {
+  fold_block(q, (int)blockIdx.x);
+}
+
+__global__ __launch_bounds__(kK2Threads) void fold_batch_kernel(
+    const Request* __restrict__ reqs, const int32_t* __restrict__ block_req, int n_blocks) {
+  if ((int)blockIdx.x >= n_blocks) return;
+  const Request& q = reqs[block_req[blockIdx.x]];
+  fold_block(q, (int)blockIdx.x - q.kf_begin);
 }
 
 // State terms of state 0 (pose, environment, self, q/qd limits, null space) are the
@@ -1137,6 +1197,7 @@ __device__ __forceinline__ GlobalStats wave_stats(const Workspace& ws, int P, fl
 // block per kWeightsPerBlock rollouts writes the weights.
 constexpr int kCostsPerThread = 32;   // costs per thread per later pass
 constexpr int kCostsAhead = 16;       // costs per thread loaded before c0 (K <= 4096)
+constexpr int kCostsByOne = kK2Threads * kCostsAhead;  // costs block 0 writes alone (4096)
 constexpr int kRowGroups = kK2Threads / kOutPerBlock;
 constexpr int kRowsAhead = 24;  // partial rows per thread loaded before the statistics
 constexpr int kWeightsPerThread = kWeightsPerBlock / kK2Threads;
@@ -1155,7 +1216,7 @@ __device__ __forceinline__ void merge_block(const DevRobot* __restrict__ rob, co
   __shared__ float red[kK2Threads];
   const int lane = threadIdx.x & (kWave - 1);
   const int tid = threadIdx.x;
-  const int K = p.K, P = p.P, HO = p.H * kNdof;
+  const int K = p.K, P = p.Pm, shift = p.m_shift, HO = p.H * kNdof;
   const int n_out_blocks = (HO + kOutPerBlock - 1) / kOutPerBlock;
 
   if (kb == 0) {
@@ -1163,15 +1224,16 @@ __device__ __forceinline__ void merge_block(const DevRobot* __restrict__ rob, co
     // --- independent fetches first: the statistics rows (wave 0) and the first
     // pass of costs to shift
     StatRows rows;
-    if (stats_out && tid < kWave) stats_load(ws, P, lane, rows);
+    if (stats_out && tid < kWave) stats_load(ws, P, shift, lane, rows);
     double sv0[kCostsAhead];
-    if (costs_out) {
+    const bool costs_here = costs_out && !(q.c0_in_ws && K > kCostsByOne);
+    if (costs_here) {
 #pragma unroll
       for (int c = 0; c < kCostsAhead; ++c) sv0[c] = ws.S[min(tid + kK2Threads * c, K - 1)];
     }
     const float c0 = q.c0_in_ws ? ws.c0[0] : state0_cost<kElemBytes>(rob, p, grid, q.state_in);
     // --- costs S = S' + c0 (eq. 28) and statistics
-    if (costs_out) {
+    if (costs_here) {
 #pragma unroll
       for (int c = 0; c < kCostsAhead; ++c) {
         const int i = tid + kK2Threads * c;
@@ -1192,7 +1254,7 @@ __device__ __forceinline__ void merge_block(const DevRobot* __restrict__ rob, co
       }
     }
     GlobalStats st{__builtin_inf(), 0.f, 0.f};
-    if (stats_out && tid < kWave) st = stats_finish(ws, P, p.k_lambda, lane, rows);
+    if (stats_out && tid < kWave) st = stats_finish(ws, P, shift, p.k_lambda, lane, rows);
     if (stats_out && tid == 0) {
       const bool ok = isfinite(st.m);
       stats_out[0] = ok ? (float)(st.m + (double)c0) : __builtin_nanf("");
@@ -1204,14 +1266,17 @@ __device__ __forceinline__ void merge_block(const DevRobot* __restrict__ rob, co
   }
 
   const int ob = kb - 1;  // output block, or weight block after them
-  if (ob >= n_out_blocks && !weights_out) return;
+  // The weight blocks also write the costs of many rollouts (one block alone takes 10 us
+  // for 65536), where the rollout launch left c0.
+  const bool costs_too = costs_out && q.c0_in_ws && K > kCostsByOne;
+  if (ob >= n_out_blocks && !weights_out && !costs_too) return;
   // The loads of this block's partial rows (or costs) are issued before the
   // statistics, which they do not depend on, so both memory rounds overlap.
   const int oi = tid % kOutPerBlock, g = tid / kOutPerBlock;
   const int o = ob * kOutPerBlock + oi;
   const bool is_out = ob < n_out_blocks;
   // This block's chunk of the block partials: [block][kOutPerBlock], contiguous.
-  const float* chunk = ws.part_N + (size_t)min(ob, n_out_blocks - 1) * P * kOutPerBlock + oi;
+  const float* chunk = ws.part_N + (size_t)min(ob, n_out_blocks - 1) * p.P * kOutPerBlock + oi;
   float nv[kRowsAhead];
   double mv[kRowsAhead];
   const int lo = (ob - n_out_blocks) * kWeightsPerBlock;
@@ -1219,15 +1284,24 @@ __device__ __forceinline__ void merge_block(const DevRobot* __restrict__ rob, co
   if (is_out) {
 #pragma unroll
     for (int c = 0; c < kRowsAhead; ++c) {
-      const int b = min(g + kRowGroups * c, P - 1);
+      const int b = min(g + kRowGroups * c, P - 1) << shift;
       nv[c] = chunk[(size_t)b * kOutPerBlock];
       mv[c] = ws.part_m[b];
     }
   } else {
 #pragma unroll
     for (int c = 0; c < kWeightsPerThread; ++c) sv[c] = ws.S[min(lo + tid + kK2Threads * c, K - 1)];
+    if (costs_too) {
+      const float c0 = ws.c0[0];
+#pragma unroll
+      for (int c = 0; c < kWeightsPerThread; ++c) {
+        const int i = lo + tid + kK2Threads * c;
+        if (i < K) costs_out[i] = (float)(sv[c] + (double)c0);
+      }
+      if (!weights_out) return;
+    }
   }
-  const GlobalStats st = wave_stats(ws, P, p.k_lambda, lane);
+  const GlobalStats st = wave_stats(ws, P, shift, p.k_lambda, lane);
   const bool ok = isfinite(st.m);
 
   if (is_out) {
@@ -1245,7 +1319,7 @@ __device__ __forceinline__ void merge_block(const DevRobot* __restrict__ rob, co
         double mb[kBatch];
 #pragma unroll
         for (int c = 0; c < kBatch; ++c) {
-          const int b = min(b0 + kRowGroups * c, P - 1);
+          const int b = min(b0 + kRowGroups * c, P - 1) << shift;
           nb[c] = chunk[(size_t)b * kOutPerBlock];
           mb[c] = ws.part_m[b];
         }
@@ -2072,6 +2146,7 @@ LaunchConfig plan_launch_config(int K, int H) {
   lc.k1_lds = k1_lds_bytes(R, H);
   lc.k2_blocks = 1 + (H * kNdof + kOutPerBlock - 1) / kOutPerBlock +
                  (K + kWeightsPerBlock - 1) / kWeightsPerBlock;
+  lc.fold_blocks = lc.P > kMaxMerged ? (lc.P + kFoldRows - 1) / kFoldRows : 0;
   return lc;
 }
 
@@ -2126,6 +2201,13 @@ int scratch_address(int device, void** out) {
   return 0;
 }
 
+// The fold of a plan step's partials, when it has one.
+static hipError_t launch_fold(const Request& q, const LaunchConfig& lc, hipStream_t s) {
+  if (!lc.fold_blocks) return hipSuccess;
+  hipLaunchKernelGGL(fold_kernel, dim3(lc.fold_blocks), dim3(kK2Threads), 0, s, q);
+  return hipGetLastError();
+}
+
 int launch_plan_step(const DevRobot* robot, const Request& q, const LaunchConfig& lc,
                      bool f16, void* stream, void* events) {
   hipStream_t s = static_cast<hipStream_t>(stream);
@@ -2138,6 +2220,7 @@ int launch_plan_step(const DevRobot* robot, const Request& q, const LaunchConfig
                      robot, q);
   if ((e = hipGetLastError()) != hipSuccess) return (int)e;
   if (ev && (e = hipEventRecord(ev[1], s)) != hipSuccess) return (int)e;
+  if ((e = launch_fold(q, lc, s)) != hipSuccess) return (int)e;
   auto k2 = f16 ? merge_kernel<2> : merge_kernel<4>;
   hipLaunchKernelGGL(k2, dim3(lc.k2_blocks), dim3(kK2Threads), 0, s, robot, q);
   if ((e = hipGetLastError()) != hipSuccess) return (int)e;
@@ -2149,8 +2232,8 @@ namespace {
 struct BatchGraph {
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
-  hipGraphNode_t up = nullptr, k1 = nullptr, k2 = nullptr, down = nullptr;
-  bool f16 = false, far = false;
+  hipGraphNode_t up = nullptr, k1 = nullptr, kf = nullptr, k2 = nullptr, down = nullptr;
+  bool f16 = false, far = false, fold = false;
 };
 
 hipKernelNodeParams kernel_node(void* func, int blocks, int threads, size_t lds, void** args) {
@@ -2176,8 +2259,8 @@ void destroy_batch_graph(void* handle) {
 
 int launch_batch_graph(void** handle, const DevRobot* robot, void* d_up, const void* h_up,
                        size_t up_bytes, const Request* reqs, const int32_t* k1_map,
-                       int k1_blocks, const int32_t* k2_map, int k2_blocks, size_t k1_lds,
-                       bool f16, bool far, void* h_res, const void* d_res, size_t res_bytes,
+                       int k1_blocks, const int32_t* k2_map, int k2_blocks, const int32_t* kf_map,
+                       int kf_blocks, size_t k1_lds, bool f16, bool far, bool fold, void* h_res, const void* d_res, size_t res_bytes,
                        void* stream) {
   void* f1 = f16 ? (far ? reinterpret_cast<void*>(rollout_cost_batch_kernel<2, true>)
                        : reinterpret_cast<void*>(rollout_cost_batch_kernel<2, false>))
@@ -2193,9 +2276,13 @@ int launch_batch_graph(void** handle, const DevRobot* robot, void* d_up, const v
   void* a2[] = {&rob, &rq, &m2};
   const hipKernelNodeParams p1 = kernel_node(f1, k1_blocks, kK1Threads, k1_lds, a1);
   const hipKernelNodeParams p2 = kernel_node(f2, k2_blocks, kK2Threads, 0, a2);
+  const int32_t* mf = kf_map;
+  void* af[] = {&rq, &mf, &kf_blocks};
+  const hipKernelNodeParams pf = kernel_node(reinterpret_cast<void*>(fold_batch_kernel),
+                                             kf_blocks > 0 ? kf_blocks : 1, kK2Threads, 0, af);
   BatchGraph* g = static_cast<BatchGraph*>(*handle);
   hipError_t e;
-  if (g && g->far != far) {  // a robot of the other pair kind: the kernel node changes
+  if (g && (g->far != far || g->fold != fold)) {  // other kernel nodes
     destroy_batch_graph(g);
     *handle = nullptr;
     g = nullptr;
@@ -2205,11 +2292,14 @@ int launch_batch_graph(void** handle, const DevRobot* robot, void* d_up, const v
     if (!g) return (int)hipErrorOutOfMemory;
     g->f16 = f16;
     g->far = far;
+    g->fold = fold;
     if ((e = hipGraphCreate(&g->graph, 0)) != hipSuccess ||
         (e = hipGraphAddMemcpyNode1D(&g->up, g->graph, nullptr, 0, d_up, h_up, up_bytes,
                                      hipMemcpyHostToDevice)) != hipSuccess ||
         (e = hipGraphAddKernelNode(&g->k1, g->graph, &g->up, 1, &p1)) != hipSuccess ||
-        (e = hipGraphAddKernelNode(&g->k2, g->graph, &g->k1, 1, &p2)) != hipSuccess ||
+        (fold && (e = hipGraphAddKernelNode(&g->kf, g->graph, &g->k1, 1, &pf)) != hipSuccess) ||
+        (e = hipGraphAddKernelNode(&g->k2, g->graph, fold ? &g->kf : &g->k1, 1, &p2)) !=
+            hipSuccess ||
         (e = hipGraphAddMemcpyNode1D(&g->down, g->graph, &g->k2, 1, h_res, d_res, res_bytes,
                                      hipMemcpyDeviceToHost)) != hipSuccess ||
         (e = hipGraphInstantiate(&g->exec, g->graph, nullptr, nullptr, 0)) != hipSuccess) {
@@ -2222,6 +2312,7 @@ int launch_batch_graph(void** handle, const DevRobot* robot, void* d_up, const v
     if ((e = hipGraphExecMemcpyNodeSetParams1D(g->exec, g->up, d_up, h_up, up_bytes,
                                                hipMemcpyHostToDevice)) != hipSuccess ||
         (e = hipGraphExecKernelNodeSetParams(g->exec, g->k1, &p1)) != hipSuccess ||
+        (fold && (e = hipGraphExecKernelNodeSetParams(g->exec, g->kf, &pf)) != hipSuccess) ||
         (e = hipGraphExecKernelNodeSetParams(g->exec, g->k2, &p2)) != hipSuccess ||
         (e = hipGraphExecMemcpyNodeSetParams1D(g->exec, g->down, h_res, d_res, res_bytes,
                                                hipMemcpyDeviceToHost)) != hipSuccess)
@@ -2338,6 +2429,7 @@ int launch_plan_step_bounds(const DevRobot* robot, const Request& q, const Launc
                        robot, q, n_k1, n_k1p, job);
     if ((e = hipGetLastError()) != hipSuccess) return (int)e;
     if (ev && (e = hipEventRecord(ev[1], s)) != hipSuccess) return (int)e;
+    if ((e = launch_fold(q, lc, s)) != hipSuccess) return (int)e;
     auto k2 = f16 ? merge_kernel<2> : merge_kernel<4>;
     hipLaunchKernelGGL(k2, dim3(lc.k2_blocks), dim3(kK2Threads), 0, s, robot, q);
     if ((e = hipGetLastError()) != hipSuccess) return (int)e;
@@ -2350,6 +2442,7 @@ int launch_plan_step_bounds(const DevRobot* robot, const Request& q, const Launc
                      robot, q);
   if ((e = hipGetLastError()) != hipSuccess) return (int)e;
   if (ev && (e = hipEventRecord(ev[1], s)) != hipSuccess) return (int)e;
+  if ((e = launch_fold(q, lc, s)) != hipSuccess) return (int)e;
   const int n_k2 = lc.k2_blocks, n_k2p = (n_k2 + kXcds - 1) / kXcds * kXcds;
   auto k2 = f16 ? merge_bounds_kernel<2> : merge_bounds_kernel<4>;
   hipLaunchKernelGGL(k2, dim3((unsigned)(n_k2p + n_bounds)), dim3(kK2Threads), 0, s, robot, q,

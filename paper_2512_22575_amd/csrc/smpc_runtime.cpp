@@ -270,6 +270,8 @@ StepParams make_params(const smpc_ctx* ctx, const smpc_plan_args* a, const Launc
   p.H = a->H;
   p.R = lc.R;
   p.P = lc.P;
+  p.Pm = lc.fold_blocks ? lc.fold_blocks : lc.P;
+  p.m_shift = lc.fold_blocks ? kFoldShift : 0;
   p.dt = a->dt;
   p.k_lambda = (float)(1.4426950408889634 / (double)a->lambda);
   return p;
@@ -927,7 +929,7 @@ struct BatchSlot {
   hipEvent_t done = nullptr;
   void* ws = nullptr;                   // half of the budget
   // Upload buffers: the batch's request descriptors, then its block maps
-  // (k1 blocks + k2 blocks int32), copied host -> device by one graph node.
+  // (k1, k2 and fold blocks, int32), copied host -> device by one graph node.
   size_t up_cap = 0;
   unsigned char* h_up = nullptr;        // pinned
   unsigned char* d_up = nullptr;
@@ -944,6 +946,7 @@ struct smpc_server {
   size_t budget = 0;
   int max_batch = 1;
   int elem_dtype = -1;
+  bool fold = false;                    // some controller's partials are folded
   std::vector<Controller> ctl;
   std::deque<smpc_request> queue;
   std::deque<smpc_completion> done;
@@ -1058,7 +1061,7 @@ smpc_status launch_next(smpc_server* s, void* stream, int* launched) {
   std::vector<int> take;
   std::vector<size_t> ws_off;
   std::vector<char> used(s->ctl.size(), 0);
-  size_t ws_total = 0, k1_total = 0, k2_total = 0;
+  size_t ws_total = 0, k1_total = 0, k2_total = 0, kf_total = 0;
   for (size_t i = 0; i < s->queue.size() && (int)take.size() < s->max_batch; ++i) {
     const smpc_request& r = s->queue[i];
     const Controller& c = s->ctl[r.controller];
@@ -1071,10 +1074,11 @@ smpc_status launch_next(smpc_server* s, void* stream, int* launched) {
     ws_total += need;
     k1_total += (size_t)c.lc.P;
     k2_total += (size_t)c.lc.k2_blocks;
+    kf_total += (size_t)c.lc.fold_blocks;
   }
   if (take.empty()) return SMPC_OK;
   const size_t req_bytes = take.size() * sizeof(Request);
-  const size_t up_bytes = req_bytes + (k1_total + k2_total) * sizeof(int32_t);
+  const size_t up_bytes = req_bytes + (k1_total + k2_total + kf_total) * sizeof(int32_t);
   if (!reserve_slot(b, up_bytes, (size_t)s->max_batch))
     return sfail(s, SMPC_E_OOM, "batch buffer allocation failed");
   Request* h_reqs = reinterpret_cast<Request*>(b.h_up);
@@ -1083,7 +1087,7 @@ smpc_status launch_next(smpc_server* s, void* stream, int* launched) {
   const int32_t* d_maps = reinterpret_cast<const int32_t*>(b.d_up + req_bytes);
 
   size_t lds = 0;
-  int k1 = 0, k2 = 0;
+  int k1 = 0, k2 = 0, kf = 0;
   b.tags.assign(take.size(), 0);
   b.ctls.assign(take.size(), 0);
   for (size_t t = 0; t < take.size(); ++t) {
@@ -1106,11 +1110,15 @@ smpc_status launch_next(smpc_server* s, void* stream, int* launched) {
                            c.lc.P);
     q.k1_begin = k1;
     q.k2_begin = k2;
+    q.kf_begin = kf;
     q.shift_out = 1;
     for (int j = 0; j < c.lc.P; ++j) h_maps[k1 + j] = (int32_t)t;
     for (int j = 0; j < c.lc.k2_blocks; ++j) h_maps[k1_total + k2 + j] = (int32_t)t;
+    for (int j = 0; j < c.lc.fold_blocks; ++j)
+      h_maps[k1_total + k2_total + kf + j] = (int32_t)t;
     k1 += c.lc.P;
     k2 += c.lc.k2_blocks;
+    kf += c.lc.fold_blocks;
     lds = std::max(lds, c.lc.k1_lds);
     c.cur ^= 1;  // the next request of this controller reads this step's result
     b.tags[t] = r.tag;
@@ -1118,9 +1126,10 @@ smpc_status launch_next(smpc_server* s, void* stream, int* launched) {
   }
   // One graph launch: descriptors and maps up, both batch kernels, results down.
   const int e = launch_batch_graph(&b.graph, s->ctx->dev_robot, b.d_up, b.h_up, up_bytes, d_reqs,
-                                   d_maps, (int)k1_total, d_maps + k1_total, (int)k2_total, lds,
+                                   d_maps, (int)k1_total, d_maps + k1_total, (int)k2_total,
+                                   d_maps + k1_total + k2_total, (int)kf_total, lds,
                                    s->elem_dtype == SMPC_GRID_F16,
-                                   robot_far_pairs(s->ctx->host_robot), b.h_res, b.d_res,
+                                   robot_far_pairs(s->ctx->host_robot), s->fold, b.h_res, b.d_res,
                                    take.size() * kResultStride * 4, stream);
   if (e != 0) return sfail(s, SMPC_E_DEVICE, std::string("batch launch failed: ") +
                                                  hipGetErrorString(static_cast<hipError_t>(e)));
@@ -1214,6 +1223,7 @@ smpc_status smpc_server_add_controller(smpc_server* s, const smpc_controller_des
       return sfail(s, SMPC_E_OOM, "controller buffers");
   }
   s->elem_dtype = d->esdf.dtype;
+  s->fold |= c.lc.fold_blocks > 0;
   s->ctl.push_back(c);
   *id_out = (int32_t)s->ctl.size() - 1;
   return SMPC_OK;
