@@ -21,7 +21,7 @@ constexpr int kWeightsPerBlock = 1024;        // weights_out elements per K2 blo
 constexpr int kFoldRows = 64;                 // block partials folded into one
 constexpr int kFoldShift = 6;
 static_assert((1 << kFoldShift) == kFoldRows, "fold width");
-constexpr int kMaxMerged = 1024;              // partials the merge reads without folding
+constexpr int kMaxMerged = 1536;              // partials the merge reads without folding
 
 // Self-collision constants of one link pair (la <= lb): bit i * kSpl + j of mask marks
 // the pair (slot la*kSpl+i, slot lb*kSpl+j).  One record, so that a group's constants

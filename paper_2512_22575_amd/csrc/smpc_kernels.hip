@@ -1127,10 +1127,11 @@ __device__ __forceinline__ GlobalStats wave_stats(const Workspace& ws, int P, in
 
 // Folds kFoldRows block partials into one, in place: rows fb kFoldRows + i, i < kFoldRows, of
 // every array into row fb kFoldRows, as the merge folds them (eqs. 29-30 regrouped).  Used
-// above kMaxMerged partials (K = 4096 at H = 64), because every wave of every merge block
-// reads all the partials it merges: the merge of the 16,384 partials of K = 65536, H = 64
+// above kMaxMerged partials, because every wave of every merge block reads all the partials
+// it merges (11.5 us at 1280 partials, 14.2 at 1536, 20.7 at 2048, against 12.4 us for fold
+// and merge and one more launch): the merge of the 16,384 partials of K = 65536, H = 64
 // took 190 us, beside 300 us of rollouts; folding them (29 MB of N, read once) and merging
-// the 256 that are left takes 9.9 + 6.2 us.  One block per row: every wave folds the
+// the 256 that are left takes 9.5 + 6.2 us.  One block per row: every wave folds the
 // statistics of the 64 rows itself (lane = row), then takes every fourth output chunk, its
 // 64 rows in eight loads of 256 contiguous bytes.
 __device__ __forceinline__ void fold_block(const Request& q, int fb) {
@@ -1159,17 +1160,29 @@ __device__ __forceinline__ void fold_block(const Request& q, int fb) {
   float f[kLoads];
 #pragma unroll
   for (int i = 0; i < kLoads; ++i) f[i] = factor[wave][g + kRowsPerLoad * i];
-  for (int ch = wave; ch < n_chunks; ch += kK2Threads / kWave) {
-    float* base = ws.part_N + ((size_t)ch * p.P + r0) * kOutPerBlock + lane % kOutPerBlock;
-    float v[kLoads], acc = 0.f;
+  constexpr int kWaves = kK2Threads / kWave, kAhead = 4;  // chunks of a wave in flight
+  for (int c0 = wave; c0 < n_chunks; c0 += kWaves * kAhead) {
+    float v[kAhead][kLoads];
 #pragma unroll
-    for (int i = 0; i < kLoads; ++i) v[i] = base[min(g + kRowsPerLoad * i, n - 1) * kOutPerBlock];
+    for (int k = 0; k < kAhead; ++k) {
+      const int ch = min(c0 + k * kWaves, n_chunks - 1);
+      const float* src = ws.part_N + ((size_t)ch * p.P + r0) * kOutPerBlock + lane % kOutPerBlock;
 #pragma unroll
-    for (int i = 0; i < kLoads; ++i)
-      if (f[i] >= 0.f) acc = fmaf(v[i], f[i], acc);
+      for (int i = 0; i < kLoads; ++i)
+        v[k][i] = src[min(g + kRowsPerLoad * i, n - 1) * kOutPerBlock];
+    }
 #pragma unroll
-    for (int off = kOutPerBlock; off < kWave; off <<= 1) acc += __shfl_xor(acc, off, kWave);
-    if (g == 0) base[0] = acc;
+    for (int k = 0; k < kAhead; ++k) {
+      const int ch = c0 + k * kWaves;
+      float acc = 0.f;
+#pragma unroll
+      for (int i = 0; i < kLoads; ++i)
+        if (f[i] >= 0.f) acc = fmaf(v[k][i], f[i], acc);
+#pragma unroll
+      for (int off = kOutPerBlock; off < kWave; off <<= 1) acc += __shfl_xor(acc, off, kWave);
+      if (g == 0 && ch < n_chunks)
+        ws.part_N[((size_t)ch * p.P + r0) * kOutPerBlock + lane] = acc;
+    }
   }
 }
 
@@ -1716,7 +1729,7 @@ rollout_bounds_kernel(const DevRobot* __restrict__ rob, const Request q, int n_k
 // Occupancy update by voxel projection (Sec. III-A) with the robot mask (Remark 2)
 // ---------------------------------------------------------------------------
 constexpr int kOgmThreads = 256;
-constexpr int kOgmPerThread = 4;  // pixels or voxels per thread, kOgmThreads apart
+constexpr int kOgmPerThread = 4;  // pixels per thread, kOgmThreads apart
 constexpr int kOgmTile = kOgmThreads * kOgmPerThread;
 
 // Robot data one thread needs for the sphere table, fetched before anything else so
@@ -1886,8 +1899,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t ogm_buffer(const void* p, uint
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
 }
 
-// Pass 2: a block takes kOgmTile consecutive voxels (x fastest), each wave 64 of them
-// per step, kOgmThreads apart over kOgmPerThread steps.  The log-odds and occupancy
+// Pass 2: a block takes kOgmVoxelTile consecutive voxels (x fastest), each wave 64 of them
+// per step, kOgmThreads apart over kOgmSteps steps.  The log-odds and occupancy
 // are accessed through buffers bounded at the block's last voxel, so the ragged end
 // needs no branch.  A wave's first voxel is split into (x, y, z) on the scalar unit;
 // a lane past the end of that row wraps into the next one (at most once, as nx >= 64;
@@ -1896,6 +1909,9 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t ogm_buffer(const void* p, uint
 // bounded buffer, so that a voxel out of view reads past the end of the image and
 // gets 0 ("no return").  Then the log-odds are updated, voxels inside the robot
 // reset and the occupancy written.
+constexpr int kOgmSteps = 4;
+constexpr int kOgmVoxelTile = kOgmThreads * kOgmSteps;
+
 __global__ __launch_bounds__(kOgmThreads) void ogm_voxel_kernel(
     const OgmArgs a, const float* __restrict__ work, float* __restrict__ log_odds,
     uint8_t* __restrict__ occ) {
@@ -1905,8 +1921,8 @@ __global__ __launch_bounds__(kOgmThreads) void ogm_voxel_kernel(
   const uint32_t npix = width * height;
   const __amdgpu_buffer_rsrc_t img = ogm_buffer(work, npix * 4u);
   const float* sph = work + npix;
-  const uint32_t blk0 = blockIdx.x * (uint32_t)kOgmTile;
-  const uint32_t nblk = min(nvox - blk0, (uint32_t)kOgmTile);
+  const uint32_t blk0 = blockIdx.x * (uint32_t)kOgmVoxelTile;
+  const uint32_t nblk = min(nvox - blk0, (uint32_t)kOgmVoxelTile);
   const __amdgpu_buffer_rsrc_t lbuf = ogm_buffer(log_odds + blk0, nblk * 4u);
   const uint32_t lane = threadIdx.x & (kWave - 1);
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -1919,15 +1935,15 @@ __global__ __launch_bounds__(kOgmThreads) void ogm_voxel_kernel(
       blo[k] = __float_as_int(sph[kOgmIndexBox + k]);
       bhi[k] = __float_as_int(sph[kOgmIndexBox + 3 + k]);
     }
-  float L[kOgmPerThread], d[kOgmPerThread], z[kOgmPerThread];
-  uint32_t vx[kOgmPerThread], vy[kOgmPerThread], vz[kOgmPerThread];
-  bool in_box[kOgmPerThread];
+  float L[kOgmSteps], d[kOgmSteps], z[kOgmSteps];
+  uint32_t vx[kOgmSteps], vy[kOgmSteps], vz[kOgmSteps];
+  bool in_box[kOgmSteps];
 #pragma unroll
-  for (int k = 0; k < kOgmPerThread; ++k)
+  for (int k = 0; k < kOgmSteps; ++k)
     L[k] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
                                          lbuf, (int)((loc + k * kOgmThreads) * 4u), 0, 0));
 #pragma unroll
-  for (int k = 0; k < kOgmPerThread; ++k) {
+  for (int k = 0; k < kOgmSteps; ++k) {
     uint32_t ix, iy, iz;
     bool box;
     if (nx >= (uint32_t)kWave) {
@@ -1979,21 +1995,25 @@ __global__ __launch_bounds__(kOgmThreads) void ogm_voxel_kernel(
     in_box[k] = box;
   }
 #pragma unroll
-  for (int k = 0; k < kOgmPerThread; ++k) {
+  for (int k = 0; k < kOgmSteps; ++k) {
     float l = L[k];
     const float e = z[k] - d[k];
     const bool hit = fabsf(e) <= a.tol, free = e < -a.tol;
-    if ((d[k] > 0.f) & (hit | free))
-      l = fminf(fmaxf(l + (hit ? a.l_hit : a.l_miss), a.l_min), a.l_max);
+    bool seen = (d[k] > 0.f) & (hit | free);
+    if (seen) l = fminf(fmaxf(l + (hit ? a.l_hit : a.l_miss), a.l_min), a.l_max);
     if (in_box[k]) {
       const float wx = a.origin[0] + ((float)vx[k] + 0.5f) * a.voxel;
       const float wy = a.origin[1] + ((float)vy[k] + 0.5f) * a.voxel;
       const float wz = a.origin[2] + ((float)vz[k] + 0.5f) * a.voxel;
-      if (in_robot_spheres(sph, wx, wy, wz)) l = a.l_min;
+      if (in_robot_spheres(sph, wx, wy, wz)) {
+        l = a.l_min;
+        seen = true;
+      }
     }
     const uint32_t o = loc + k * kOgmThreads;
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, l), lbuf, (int)(o * 4u),
-                                          0, 0);
+    if (seen)  // others keep their value
+      __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, l), lbuf, (int)(o * 4u),
+                                            0, 0);
     if (occ)
       __builtin_amdgcn_raw_buffer_store_b8((uint8_t)(l > a.l_occ ? 1 : 0),
                                            ogm_buffer(occ + blk0, nblk), (int)o, 0, 0);
@@ -2005,8 +2025,11 @@ __global__ __launch_bounds__(kOgmThreads) void ogm_voxel_kernel(
 // one row, 16 bytes of log-odds and one occupancy word per group (plain global
 // accesses guarded by the group count: groups are whole); the index split and the
 // affine map are evaluated once per group (X, Y, Z of the next voxel differ by the
-// first column of M).  Otherwise as ogm_voxel_kernel.
-constexpr int kOgmGroups = 2;
+// first column of M).  Otherwise as ogm_voxel_kernel.  Bound by the chain load, project,
+// gather, store of each wave, so one group per lane and many short waves: 200^3 with a
+// 640x480 image takes 16.2 us (54 MB moved, 3.3 TB/s; 21.5 us with two groups per lane and
+// every log-odds written back, 19.3 us with two, 28.7 us with four).
+constexpr int kOgmGroups = 1;
 constexpr int kOgmGroupTile = kOgmThreads * kOgmGroups;  // groups per block
 
 __global__ __launch_bounds__(kOgmThreads) void ogm_voxel4_kernel(
@@ -2031,7 +2054,7 @@ __global__ __launch_bounds__(kOgmThreads) void ogm_voxel4_kernel(
   const uint32_t tid = threadIdx.x;
   float L[kOgmGroups][4], d[kOgmGroups][4], z[kOgmGroups][4];
   uint32_t gx[kOgmGroups], gy[kOgmGroups], gz[kOgmGroups];
-  bool row_box[kOgmGroups];
+  bool viewed[kOgmGroups], row_box[kOgmGroups];
 #pragma unroll
   for (int k = 0; k < kOgmGroups; ++k) {
     const uint32_t g = blk_g + tid + k * kOgmThreads;
@@ -2057,6 +2080,8 @@ __global__ __launch_bounds__(kOgmThreads) void ogm_voxel4_kernel(
     const float X0 = fmaf(a.M[0], fx, fmaf(a.M[1], fy, fmaf(a.M[2], fz, a.m[0])));
     const float Y0 = fmaf(a.M[3], fx, fmaf(a.M[4], fy, fmaf(a.M[5], fz, a.m[1])));
     const float Z0 = fmaf(a.M[6], fx, fmaf(a.M[7], fy, fmaf(a.M[8], fz, a.m[2])));
+    uint32_t off[4];
+    bool any = false;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const float X = fmaf((float)j, a.M[0], X0);
@@ -2068,36 +2093,61 @@ __global__ __launch_bounds__(kOgmThreads) void ogm_voxel4_kernel(
       const bool in_view =
           (Z > 1.17549435e-38f) & ((uint32_t)pu < width) & ((uint32_t)pv < height);
       // pixel row and column are below 2^14: a 24-bit multiply is exact
-      const uint32_t off = in_view ? __umul24((uint32_t)pv, width) + (uint32_t)pu : npix;
-      d[k][j] = __builtin_bit_cast(
-          float, __builtin_amdgcn_raw_buffer_load_b32(img, (int)(off * 4u), 0, 0));
+      off[j] = in_view ? __umul24((uint32_t)pv, width) + (uint32_t)pu : npix;
+      any |= in_view;
       z[k][j] = Z;
+      d[k][j] = 0.f;
+    }
+    // A wave holds 256 voxels of one or two rows; where none is in view (half of the
+    // waves of a 200^3 map around the arm) it skips the gathers and the update below.
+    viewed[k] = any_lane(any);
+    if (viewed[k]) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        d[k][j] = __builtin_bit_cast(
+            float, __builtin_amdgcn_raw_buffer_load_b32(img, (int)(off[j] * 4u), 0, 0));
     }
   }
 #pragma unroll
   for (int k = 0; k < kOgmGroups; ++k) {
-    uint32_t bits = 0u;
-    float out[4];
+    float l[4];
+    bool seen = false;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      float l = L[k][j];
-      const float e = z[k][j] - d[k][j];
-      const bool hit = fabsf(e) <= a.tol, free = e < -a.tol;
-      if ((d[k][j] > 0.f) & (hit | free))
-        l = fminf(fmaxf(l + (hit ? a.l_hit : a.l_miss), a.l_min), a.l_max);
-      const int32_t ix = (int32_t)(gx[k] + j);
-      if (row_box[k] & (ix >= blo[0]) & (ix <= bhi[0])) {
-        const float wx = a.origin[0] + ((float)ix + 0.5f) * a.voxel;
-        const float wy = a.origin[1] + ((float)gy[k] + 0.5f) * a.voxel;
-        const float wz = a.origin[2] + ((float)gz[k] + 0.5f) * a.voxel;
-        if (in_robot_spheres(sph, wx, wy, wz)) l = a.l_min;
+    for (int j = 0; j < 4; ++j) l[j] = L[k][j];
+    if (viewed[k]) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float e = z[k][j] - d[k][j];
+        const bool hit = fabsf(e) <= a.tol, free = e < -a.tol;
+        const bool upd = (d[k][j] > 0.f) & (hit | free);
+        const float v = fminf(fmaxf(l[j] + (hit ? a.l_hit : a.l_miss), a.l_min), a.l_max);
+        l[j] = upd ? v : l[j];
+        seen |= upd;
       }
-      out[j] = l;
-      bits |= (l > a.l_occ ? 1u : 0u) << (8 * j);
     }
+    if (any_lane(row_box[k])) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int32_t ix = (int32_t)(gx[k] + j);
+        if (row_box[k] & (ix >= blo[0]) & (ix <= bhi[0])) {
+          const float wx = a.origin[0] + ((float)ix + 0.5f) * a.voxel;
+          const float wy = a.origin[1] + ((float)gy[k] + 0.5f) * a.voxel;
+          const float wz = a.origin[2] + ((float)gz[k] + 0.5f) * a.voxel;
+          if (in_robot_spheres(sph, wx, wy, wz)) {
+            l[j] = a.l_min;
+            seen = true;
+          }
+        }
+      }
+    }
+    uint32_t bits = 0u;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) bits |= (l[j] > a.l_occ ? 1u : 0u) << (8 * j);
     const uint32_t g = blk_g + tid + k * kOgmThreads;
     if (g < ngroups) {
-      L4[g] = make_float4(out[0], out[1], out[2], out[3]);
+      // A group with no update and no reset keeps its values: 56 % of a 200^3 map is out of
+      // the reference camera's view, 18 MB of the 72 MB the pass would move.
+      if (seen) L4[g] = make_float4(l[0], l[1], l[2], l[3]);
       if (occ) occ4[g] = bits;
     }
   }
@@ -2347,7 +2397,8 @@ int launch_ogm(const DevRobot* robot, const OgmArgs& a, const float* depth, floa
                        dim3((unsigned)((ngroups + kOgmGroupTile - 1) / kOgmGroupTile)),
                        dim3(kOgmThreads), 0, stream, a, work, log_odds, occ);
   } else {
-    hipLaunchKernelGGL(ogm_voxel_kernel, dim3((unsigned)((nvox + kOgmTile - 1) / kOgmTile)),
+    hipLaunchKernelGGL(ogm_voxel_kernel,
+                       dim3((unsigned)((nvox + kOgmVoxelTile - 1) / kOgmVoxelTile)),
                        dim3(kOgmThreads), 0, stream, a, work, log_odds, occ);
   }
   return hipGetLastError() == hipSuccess ? 0 : -1;

@@ -11,8 +11,9 @@ from tests.gpu_helpers import U_ATOL
 
 pytestmark = pytest.mark.gpu
 
-# H = 64: 4 rollouts per partial, so 4097 rollouts are 1025 partials, the first folded ones.
-CASES = [(4096, 64), (4097, 64), (4352, 64), (4353, 64), (12345, 40), (70001, 3)]
+# H = 64: 4 rollouts per partial, so 6145 rollouts are 1537 partials, the first folded ones
+# (25 groups, the last of one row); 6400 and 6401 end a group of 64 and begin one.
+CASES = [(6144, 64), (6145, 64), (6400, 64), (6401, 64), (12345, 40), (70001, 3)]
 
 
 def _check(S, out, noise, U_bar, lam):
@@ -77,7 +78,7 @@ def test_served_with_small_controllers():
 
     from paper_2512_22575_amd import smpc as S
     dev = torch.device("cuda:0")
-    sizes = [(256, 16), (4353, 64), (1024, 32)]
+    sizes = [(256, 16), (6401, 64), (1024, 32)]
     inps = [W.make_inputs(40 + i, K=K, H=H, dt=0.02, n=32, voxel=0.05, n_boxes=4, n_spheres=4,
                           robot_seed=40) for i, (K, H) in enumerate(sizes)]
     planner = S.Planner(inps[0].robot, device=0)
