@@ -25,8 +25,8 @@
 // per sample: split over 16 lanes per line they took 75 us (y) and 107 us (z) of a 200^3
 // field of 40 obstacles, at 150 VALU and as many SALU instructions per output.  They use
 // the other property of the same minimisation, that the minimiser over q moves right with
-// p (transform_lines): 53 and 57 us on the same grid, VALU issue (138 instructions per 64
-// outputs, 28 us of it) and the waves' LDS latency being the bound.
+// p (transform_lines): 49 and 54 us on the same grid, VALU issue (half of the time) and
+// the waves' LDS latency being the bound.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -282,11 +282,10 @@ __device__ __forceinline__ int opaque(int x) {
 }
 
 // Minima over rows lo .. hi (rows past hi are candidates like any other, at worst padding)
-// of word(q) + (p^2 - 2 p q) << kShift for the kLeaf outputs p from p0 on, less p^2: four
-// rows per round, every row serving all outputs.  word(v, q): the tile word v of row q.
-template <class Word>
+// of the tile word plus (p^2 - 2 p q) << kShift for the kLeaf outputs p from p0 on, less
+// p^2: four rows per round, every row serving all outputs.
 __device__ __forceinline__ void leaf_minima(const int* col, int p0, int lo, int hi,
-                                            int (&acc)[kLeaf], Word&& word) {
+                                            int (&acc)[kLeaf]) {
 #pragma unroll
   for (int j = 0; j < kLeaf; ++j) acc[j] = 0x7FFFFFFF;
   const int s0 = p0 << (kShift + 1), s1 = -s0, s2 = -2 * s0, s3 = -3 * s0;
@@ -296,8 +295,7 @@ __device__ __forceinline__ void leaf_minima(const int* col, int p0, int lo, int 
     const int v0 = opaque(q << (kShift + 1)), v1 = opaque(v0 + (1 << (kShift + 1))),
               v2 = opaque(v0 + (2 << (kShift + 1))), v3 = opaque(v0 + (3 << (kShift + 1)));
     const int m = opaque(__mul24(q, s1));
-    int b0 = word(g0, q) + m, b1 = word(g1, q + 1) + m + s1, b2 = word(g2, q + 2) + m + s2,
-        b3 = word(g3, q + 3) + m + s3;
+    int b0 = g0 + m, b1 = g1 + m + s1, b2 = g2 + m + s2, b3 = g3 + m + s3;
 #pragma unroll
     for (int j = 0; j < kLeaf; ++j) {
       acc[j] = min3(min3(acc[j], b0, b1), b2, b3);
@@ -341,48 +339,61 @@ __device__ __forceinline__ void transform_lines(int* lds, int n, Load&& load, De
       occ_rows = (occ_rows << 1) | (occ ? 1u : 0u);
     }
   }
-  auto pad = [&](bool far_in) {  // rows after the line: no source of the field at hand
-#pragma unroll
-    for (int k = 0; k < kPad; ++k)
-      col[(n + k) * kLines] = far_in ? ~kFar : (kFar + (n + k) * (n + k)) << kShift;
-  };
   if (team == 0) {
-    pad(true);
+#pragma unroll
+    for (int k = 0; k < kPad; ++k)  // rows after the line: no source
+      col[(n + k) * kLines] = (kFar + (n + k) * (n + k)) << kShift;
     cut[0] = 0;                            // minimisers before the first cut and after the
     cut[nleaf * kLines] = (Index)(n - 1);  // last one: the ends of the line bound them
   }
-  // D_in at the occupied voxels: f_in is 0 on free voxels.  D_in(p) is at most f_in(p), and
-  // at most the squared distance to any free row, so only nearby rows matter (obstacles
-  // are thin against a line).
+  // D_in at the occupied voxels, f_in being 0 on free ones: the rows of a leaf first, then
+  // outward from it (obstacles are thin against a line) until no farther row can matter to
+  // any lane.  A row index clamped into the line is a candidate at more than its true
+  // cost, which changes nothing.  Blocks inside obstacles are the last to end, and this is
+  // what they spend their time on: with the test of the reach before each pair of rows, and
+  // no loop before it, the 200^3 passes went from 53 and 57 us to 49 and 54.
   if (block_any<kMaxWaves>(occ_rows != 0u)) {
     for (int i = team; i < nleaf; i += teams) {
       const int p0 = i * kLeaf;
-      int own[kLeaf], most = -1, least = kFar;  // f_in at the occupied voxels, negative at free ones
+      int own[kLeaf], acc[kLeaf], most = -1;  // own: f_in at occupied voxels, negative at free ones
 #pragma unroll
       for (int j = 0; j < kLeaf; ++j) own[j] = ~col[min(p0 + j, n - 1) * kLines];
 #pragma unroll
-      for (int j = 0; j < kLeaf; ++j) {
-        most = max(most, own[j]);
-        least = min(least, own[j]);
-      }
+      for (int j = 0; j < kLeaf; ++j) most = max(most, own[j]);
       if (most < 0) continue;
-      int reach = min((int)sqrtf((float)most) + 1, n);
-      if (least < 0) {
-        reach = min(reach, kLeaf - 1);  // a free row among the outputs
-      } else {
 #pragma unroll
-        for (int d = 16; d >= 4; d -= 4) {  // a free row d from the nearer end?
-          const int w = max(col[max(p0 - d, 0) * kLines], col[min(p0 + kLeaf - 1 + d, n - 1) * kLines]);
-          if (w >= 0) reach = min(reach, d + kLeaf - 1);
+      for (int j = 0; j < kLeaf; ++j) {
+        acc[j] = max(own[j], 0);
+#pragma unroll
+        for (int k = 0; k < kLeaf; k += 2)
+          acc[j] = min3(acc[j], max(own[k], 0) + (j - k) * (j - k),
+                        max(own[k + 1], 0) + (j - k - 1) * (j - k - 1));
+      }
+      const int dmax = max(p0, n - p0 - kLeaf);  // rows on the longer side
+      for (int d = 1; d <= dmax; d += 2) {
+        // Every output's rows nearer than d are in.
+        int worst = acc[0];
+#pragma unroll
+        for (int j = 1; j < kLeaf; ++j) worst = max(worst, acc[j]);
+        if (worst <= d * d) break;
+        int f[4];
+        f[0] = col[max(p0 - d, 0) * kLines];
+        f[1] = col[max(p0 - d - 1, 0) * kLines];
+        f[2] = col[min(p0 + kLeaf - 1 + d, n - 1) * kLines];
+        f[3] = col[min(p0 + kLeaf + d, n - 1) * kLines];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) f[c] = max(~f[c], 0);
+#pragma unroll
+        for (int j = 0; j < kLeaf; ++j) {
+          const int lo = d + j, hi = d + kLeaf - 1 - j;
+          acc[j] = min3(acc[j], f[0] + lo * lo, f[1] + (lo + 1) * (lo + 1));
+          acc[j] = min3(acc[j], f[2] + hi * hi, f[3] + (hi + 1) * (hi + 1));
         }
       }
-      int acc[kLeaf];
-      leaf_minima(col, p0, max(p0 - reach, 0), min(p0 + kLeaf - 1 + reach, n - 1), acc,
-                  [](int w, int q) { return (max(~w, 0) + __mul24(q, q)) << kShift; });
 #pragma unroll
       for (int j = 0; j < kLeaf; ++j) {
         const int p = p0 + j;
-        if (p < n && own[j] >= 0) emit(p, (uint32_t)((acc[j] >> kShift) + p * p), true);
+        if (p < n && own[j] >= 0) emit(p, (uint32_t)acc[j], true);
       }
     }
     __syncthreads();
@@ -391,10 +402,8 @@ __device__ __forceinline__ void transform_lines(int* lds, int n, Load&& load, De
       const int q = min(row0 + kRows - 1 - __builtin_ctz(rows), n - 1);
       col[q * kLines] = (__mul24(q, q) << kShift) | 1;
     }
+    __syncthreads();
   }
-  if (team == 0) pad(false);
-  __syncthreads();
-
   // The minimiser at the unit's first output, over the whole line (the first unit's is
   // bounded by row 0 instead), eight reads in flight.
   if (row0 > 0 && row0 < n) {
@@ -437,8 +446,7 @@ __device__ __forceinline__ void transform_lines(int* lds, int n, Load&& load, De
   for (int i = team; i < nleaf; i += teams) {
     const int p0 = i * kLeaf;
     int acc[kLeaf];
-    leaf_minima(col, p0, cut[i * kLines], cut[(i + 1) * kLines], acc,
-                [](int w, int) { return w; });
+    leaf_minima(col, p0, cut[i * kLines], cut[(i + 1) * kLines], acc);
     int own[kLeaf];
 #pragma unroll
     for (int j = 0; j < kLeaf; ++j) own[j] = col[min(p0 + j, n - 1) * kLines];
