@@ -25,8 +25,8 @@
 // per sample: split over 16 lanes per line they took 75 us (y) and 107 us (z) of a 200^3
 // field of 40 obstacles, at 150 VALU and as many SALU instructions per output.  They use
 // the other property of the same minimisation, that the minimiser over q moves right with
-// p (transform_lines): 49 and 54 us on the same grid, VALU issue (half of the time) and
-// the waves' LDS latency being the bound.
+// p (transform_lines): 48 and 53 us on the same grid.  All blocks of such a grid run at
+// once, and those inside obstacles end last (the slowest waves take twice the mean).
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -365,20 +365,22 @@ __device__ __forceinline__ void transform_lines(int* lds, int n, Load&& load, De
   // The minimiser at the unit's first output, over the whole line (the first unit's is
   // bounded by row 0 instead), eight reads in flight.
   if (row0 > 0 && row0 < n) {
-    int best = 0x7FFFFFFF, t = 0;  // t = (p^2 - 2 p q) << kShift | 2 q, less the p^2 term
-    const int dt = 2 - (row0 << (kShift + 1));
-    int q = 0;
-    for (; q + 8 <= n; q += 8) {
-      const int* r = col + q * kLines;
+    int best = 0x7FFFFFFF;
+    const int dt = 2 - (row0 << (kShift + 1));  // row q adds q dt: (p^2 - 2 p q) << kShift | 2 q, less p^2
+    int ct[8];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) ct[c] = opaque(c * dt);
+    const int* r = col;
+    int t = 0;
+    for (int left = n / 8; left > 0; --left, r += 8 * kLines) {
       int g[8];
 #pragma unroll
       for (int c = 0; c < 8; ++c) g[c] = r[c * kLines];
 #pragma unroll
-      for (int c = 0; c < 8; c += 2)
-        best = min3(best, g[c] + (t + c * dt), g[c + 1] + (t + (c + 1) * dt));
-      t += 8 * dt;
+      for (int c = 0; c < 8; c += 2) best = min3(best, g[c] + ct[c] + t, g[c + 1] + ct[c + 1] + t);
+      t = opaque(t + 8 * dt);
     }
-    for (; q < n; ++q, t += dt) best = min(best, col[q * kLines] + t);
+    for (int q = n & ~7; q < n; ++q, t += dt, r += kLines) best = min(best, r[0] + t);
     cut[team * kPer * kLines] = (Index)key_row(best);
   }
   __syncthreads();
