@@ -209,10 +209,12 @@ static_assert(((long long)kFar + (kEdtMaxSide + kPad) * (kEdtMaxSide + kPad)) <<
 // A team stages one unit of kPer leaves of its block's lines and searches the minimiser at
 // the unit's first output over the whole line; the cuts in between and the leaves are
 // dealt to the teams in turn (obstacles and far regions cover neighbouring outputs).
-// kPer = 1, 2, 4 for lines of up to 64, 128 and 512 samples: about eight teams (four
-// waves) per block, so that small grids still fill the chip.
+// kPer = 1, 2, 4 for lines of up to 64, 256 and 512 samples, at most eight waves per
+// block: small grids still fill the chip, and a block inside an obstacle, which the pass
+// ends with, has twice the waves that kPer = 4 gives it at 200 samples (field of 200^3: 103.1 us;
+// kPer = 4 from 129 samples on: 104.8).
 __host__ __device__ constexpr int line_leaves(int n) { return (n + kLeaf - 1) / kLeaf; }
-__host__ __device__ constexpr int unit_leaves(int n) { return n <= 64 ? 1 : n <= 128 ? 2 : 4; }
+__host__ __device__ constexpr int unit_leaves(int n) { return n <= 64 ? 1 : n <= 256 ? 2 : 4; }
 __host__ __device__ constexpr int line_waves(int n) {
   return ((line_leaves(n) + unit_leaves(n) - 1) / unit_leaves(n) + 1) / 2;
 }
@@ -529,12 +531,10 @@ void launch_pass_z(const uint32_t* yrec, int nx, int ny, int nz, const FieldOut&
 void launch_line_passes(const uint16_t* xrec, uint32_t* yrec, int nx, int ny, int nz,
                         const FieldOut& fo, hipStream_t stream) {
   const auto y = ny <= 64    ? launch_pass_y<1, uint8_t>
-                 : ny <= 128 ? launch_pass_y<2, uint8_t>
-                 : ny <= 256 ? launch_pass_y<4, uint8_t>
+                 : ny <= 256 ? launch_pass_y<2, uint8_t>
                              : launch_pass_y<4, uint16_t>;
   const auto z = nz <= 64    ? launch_pass_z<1, uint8_t>
-                 : nz <= 128 ? launch_pass_z<2, uint8_t>
-                 : nz <= 256 ? launch_pass_z<4, uint8_t>
+                 : nz <= 256 ? launch_pass_z<2, uint8_t>
                              : launch_pass_z<4, uint16_t>;
   y(xrec, yrec, nx, ny, nz, stream);
   z(yrec, nx, ny, nz, fo, stream);
