@@ -434,8 +434,13 @@ __device__ __forceinline__ uint32_t xcd_tile() {
   const uint32_t b = blockIdx.x, k = b / 8;  // k-th tile of this XCD
   return ((b % 8) + 8 * (k / G)) * G + k % G;
 }
-// Tiles per 128-byte line: 32 lines x 2-byte x-records, 32 lines x 4-byte y-records.
-constexpr int kGroupY = 2, kGroupZ = 1;
+// In a grid whose rows do not start on 128-byte lines, each tile shares the first and the last
+// line of every row with its neighbours, and two halves of a line written through different
+// L2s go to memory twice (z pass of 333x257x141: 3.5 M write requests for 2.3 M lines' worth).
+// Field of 333x257x141 by tiles per group: 182.1 us (2 and 1, what aligned rows need), 164.4
+// (4), 161.4 (8), 161.3 (16); 200^3, whose rows are aligned in the z pass: 103.2, 102.7, 103.3,
+// 104.3.
+constexpr int kGroup = 8;
 
 // The element `off` bytes after a uniform base (off < 2^32).
 template <class T>
@@ -452,7 +457,7 @@ template <int kPer, class Index>
 __global__ __launch_bounds__(64 * kMaxWaves) void edt_pass_y_kernel(
     const uint16_t* __restrict__ xrec, uint32_t* __restrict__ yrec, int nx, int ny, int nz) {
   extern __shared__ int lds[];
-  const uint32_t lines = (uint32_t)nx * nz, tile = xcd_tile<kGroupY>();
+  const uint32_t lines = (uint32_t)nx * nz, tile = xcd_tile<kGroup>();
   if (tile * kLines >= lines) return;  // whole block
   const uint32_t l = min(tile * kLines + threadIdx.x % kLines, lines - 1u);
   const uint32_t z = l / (uint32_t)nx, x = l - z * nx;
@@ -499,7 +504,7 @@ template <int kPer, class Index>
 __global__ __launch_bounds__(64 * kMaxWaves) void edt_pass_z_kernel(
     const uint32_t* __restrict__ yrec, int nx, int ny, int nz, FieldOut fo) {
   extern __shared__ int lds[];
-  const uint32_t plane = (uint32_t)nx * ny, tile = xcd_tile<kGroupZ>();
+  const uint32_t plane = (uint32_t)nx * ny, tile = xcd_tile<kGroup>();
   if (tile * kLines >= plane) return;  // whole block
   const uint32_t at = min(tile * kLines + threadIdx.x % kLines, plane - 1u);
   transform_lines<kPer, Index>(
@@ -515,7 +520,7 @@ template <int kPer, class Index>
 void launch_pass_y(const uint16_t* xrec, uint32_t* yrec, int nx, int ny, int nz,
                    hipStream_t stream) {
   const long long tiles = ((long long)nx * nz + kLines - 1) / kLines;
-  hipLaunchKernelGGL((edt_pass_y_kernel<kPer, Index>), dim3((unsigned)xcd_blocks<kGroupY>(tiles)),
+  hipLaunchKernelGGL((edt_pass_y_kernel<kPer, Index>), dim3((unsigned)xcd_blocks<kGroup>(tiles)),
                      dim3(64 * line_waves(ny)), line_lds_bytes<Index>(ny), stream, xrec, yrec, nx,
                      ny, nz);
 }
@@ -523,7 +528,7 @@ template <int kPer, class Index>
 void launch_pass_z(const uint32_t* yrec, int nx, int ny, int nz, const FieldOut& fo,
                    hipStream_t stream) {
   const long long tiles = ((long long)nx * ny + kLines - 1) / kLines;
-  hipLaunchKernelGGL((edt_pass_z_kernel<kPer, Index>), dim3((unsigned)xcd_blocks<kGroupZ>(tiles)),
+  hipLaunchKernelGGL((edt_pass_z_kernel<kPer, Index>), dim3((unsigned)xcd_blocks<kGroup>(tiles)),
                      dim3(64 * line_waves(nz)), line_lds_bytes<Index>(nz), stream, yrec, nx, ny,
                      nz, fo);
 }
