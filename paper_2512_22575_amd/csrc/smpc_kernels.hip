@@ -1420,12 +1420,10 @@ __global__ __launch_bounds__(256) void sample_noise_kernel(uint32_t k0, uint32_t
 }
 
 // float32 -> float16 grid: clamp to [-clamp, clamp], round to nearest even.
-// Coarse lower bounds (smpc_grid_coarse_min): one block per row (cy, cz) of cells.
-// Each thread folds one x column of the rows y in [8 cy, 8 cy + 8], z in
-// [8 cz, 8 cz + 8] (clamped to the grid) -- minimum, largest |phi|, any non-finite
-// value -- with a batch of loads in flight; then each cell combines its 9 columns
-// [8 cx, 8 cx + 8] through LDS.  The x axis is covered in chunks of 31 cells (249
-// columns).  A non-finite value anywhere in a cell's window makes its bound -inf.
+// Coarse lower bounds (smpc_grid_coarse_min).  A cell's bound is the minimum of its window
+// less a margin of the largest |phi| there; a non-finite value anywhere in the window
+// makes it -inf.
+//
 // A ball of query points in continuous-index units (u = (p - origin) / voxel - 1/2
 // per axis): centre c and radius r; r = inf takes every cell.  Cell k along an axis
 // (nk cells) holds the lookups with u in [8k, 8k + 8), extended to -inf for k = 0 and
@@ -1444,75 +1442,42 @@ __device__ __forceinline__ float coarse_axis_gap(float c, int k0, int k1, int nk
   return d * d;
 }
 
-constexpr int kCoarseThreads = 256;
-constexpr int kCellsPerChunk = (kCoarseThreads - 1) / kCoarseCell;  // 31
-
+// Rows shorter than one 16-byte group, i.e. one cell long: a wave per cell (cy, cz), its
+// lanes over the window's voxels.
 template <int kElemBytes>
-__global__ __launch_bounds__(kCoarseThreads) void grid_coarse_min_kernel(
-    const void* __restrict__ grid, uint32_t grid_bytes, int nx, int ny, int nz, int ncx,
-    int ncy, int ncz, CoarseBall ball, float* __restrict__ out) {
-  __shared__ float col_min[kCoarseThreads], col_max[kCoarseThreads];
-  __shared__ int col_bad[kCoarseThreads];
-  const int cy = blockIdx.x % ncy, cz = blockIdx.x / ncy;
+__global__ __launch_bounds__(kWave) void grid_coarse_min_short_kernel(
+    const void* __restrict__ grid, uint32_t grid_bytes, int nx, int ny, int nz, int ncy, int ncz,
+    CoarseBall ball, float* __restrict__ out) {
+  static_assert(16 / kElemBytes <= kCoarseCell, "such a row is one cell");
+  const int cy = blockIdx.x % ncy, cz = blockIdx.x / ncy, lane = threadIdx.x;
   const int y0 = cy * kCoarseCell, z0 = cz * kCoarseCell;
   const int wy = min(y0 + kCoarseCell, ny - 1) - y0 + 1;
   const int wz = min(z0 + kCoarseCell, nz - 1) - z0 + 1;
-  const int rows = wy * wz;
   const __amdgpu_buffer_rsrc_t rsrc = grid_resource(grid, grid_bytes);
-  const int tid = threadIdx.x;
-  if (coarse_axis_gap(ball.c[0], 0, ncx - 1, ncx) + coarse_axis_gap(ball.c[1], cy, cy, ncy) +
-          coarse_axis_gap(ball.c[2], cz, cz, ncz) > ball.r2) {
-    // No lookup from the ball reaches this row of cells: no bound (never skips).
-    for (int cx = tid; cx < ncx; cx += kCoarseThreads)
-      out[((long long)cz * ncy + cy) * ncx + cx] = -__builtin_inff();
-    return;
+  float mn = __builtin_inff(), mx = 0.f;
+  bool bad = false;
+  for (int i = lane; i < wy * wz * nx; i += kWave) {
+    const int r = i / nx, x = i - r * nx, z = z0 + r / wy, y = y0 + r % wy;
+    const float v =
+        load_grid<kElemBytes>(rsrc, (uint32_t)(((long long)z * ny + y) * nx + x) * kElemBytes, 0u);
+    bad |= !isfinite(v);
+    mn = fminf(mn, v);
+    mx = fmaxf(mx, fabsf(v));
   }
-  for (int cx0 = 0; cx0 < ncx; cx0 += kCellsPerChunk) {
-    const int x0 = cx0 * kCoarseCell;
-    const int x = min(x0 + tid, nx - 1);
-    float mn = __builtin_inff(), mx = 0.f;
-    bool bad = false;
-    constexpr int kBatch = 27;
-    for (int r0 = 0; r0 < rows; r0 += kBatch) {
-      float v[kBatch];
 #pragma unroll
-      for (int c = 0; c < kBatch; ++c) {
-        const int r = min(r0 + c, rows - 1);
-        const int y = y0 + r % wy, z = z0 + r / wy;
-        const uint32_t off = (uint32_t)(((long long)z * ny + y) * nx + x) * kElemBytes;
-        v[c] = load_grid<kElemBytes>(rsrc, off, 0u);
-      }
-#pragma unroll
-      for (int c = 0; c < kBatch; ++c) {
-        bad |= !isfinite(v[c]);
-        mn = fminf(mn, v[c]);
-        mx = fmaxf(mx, fabsf(v[c]));
-      }
-    }
-    col_min[tid] = mn;
-    col_max[tid] = mx;
-    col_bad[tid] = bad;
-    __syncthreads();
-    const int cx = cx0 + tid;
-    if (tid < kCellsPerChunk && cx < ncx) {
-      const int c_lo = tid * kCoarseCell;
-      const int c_hi = min(x0 + c_lo + kCoarseCell, nx - 1) - x0;  // last column, chunk-relative
-      float cmn = __builtin_inff(), cmx = 0.f;
-      bool cbad = false;
-      for (int c = c_lo; c <= c_hi; ++c) {
-        cmn = fminf(cmn, col_min[c]);
-        cmx = fmaxf(cmx, col_max[c]);
-        cbad |= col_bad[c] != 0;
-      }
-      out[((long long)cz * ncy + cy) * ncx + cx] =
-          cbad ? -__builtin_inff() : cmn - (1e-5f + cmx * 0x1p-18f);
-    }
-    __syncthreads();
+  for (int off = kWave / 2; off > 0; off >>= 1) {
+    mn = fminf(mn, __shfl_xor(mn, off, kWave));
+    mx = fmaxf(mx, __shfl_xor(mx, off, kWave));
   }
+  // No lookup from the ball reaches this cell: no bound (never skips).
+  if (coarse_axis_gap(ball.c[0], 0, 0, 1) + coarse_axis_gap(ball.c[1], cy, cy, ncy) +
+          coarse_axis_gap(ball.c[2], cz, cz, ncz) > ball.r2)
+    bad = true;
+  bad = any_lane(bad);
+  if (lane == 0) out[blockIdx.x] = bad ? -__builtin_inff() : mn - (1e-5f + mx * 0x1p-18f);
 }
 
-// Coarse lower bounds, wide path: rows whose byte length is a multiple of 16 in a
-// 16-byte-aligned grid.  A block covers one row (cy, cz) of cells and a chunk of
+// Coarse lower bounds of all other rows.  A block covers one row (cy, cz) of cells and a chunk of
 // kCoarseChunkGroups - 1 sixteen-byte groups of columns (31 cells of float32, 63 of
 // float16) plus the next group, whose first column closes the chunk's last window.
 // Wave s of a block of kWaves waves loads group g (its lane) of the 9 rows of planes
@@ -1531,6 +1496,7 @@ constexpr int kCoarseSubsets = 5;
 constexpr int kCoarseWideThreads = kCoarseChunkGroups * kCoarseSubsets;  // 320
 constexpr int kXcds = 8;
 typedef uint32_t U32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t U32x4Any __attribute__((ext_vector_type(4), aligned(1)));  // at any address
 
 // One wide-path bounds job: the grid, its cell counts, the work items (chunks x cell
 // rows) and the ball the bounds are restricted to.
@@ -1548,16 +1514,23 @@ struct CoarseJob {
 // and over its first column alone.  For a float the bits with the sign cleared order like
 // |phi| when finite and are >= 0x7f800000 for +-inf and NaN, so one unsigned maximum
 // gives max |phi| and flags any non-finite value.
+//
+// kRagged: rows that are not whole groups, or do not start on a 16-byte boundary, with
+// unaligned loads.  The row's last group is loaded so that it ends with the row: its first `before`
+// columns are the previous group's, and the row's last column takes their places.  A
+// block per row of cells, a voxel per lane and load, 27 loads at once, took 8.1 us of a
+// 150x150x25 grid; this takes 4.2.  Rows of whole groups keep their own kernel, which does
+// without the selects and is the one that plan steps launch with their rollouts or merge.
 struct CoarseFold {
   float mn, fmn;
   uint32_t mxb, fmxb;
 };
 
-template <int kElemBytes, int kP>
+template <int kElemBytes, int kP, bool kRagged>
 __device__ __forceinline__ CoarseFold coarse_fold(const unsigned char* __restrict__ grid,
                                                   size_t plane_bytes, size_t row_bytes, int z0,
                                                   int wz, int y0, int wy, int s, int kWaves,
-                                                  uint32_t lane_off) {
+                                                  uint32_t lane_off, int before) {
   constexpr int kCols = 16 / kElemBytes;
   // Non-temporal loads: the grid streams through once and does not displace what the
   // plan step that follows keeps in L2 (robot constants, instructions).
@@ -1569,7 +1542,10 @@ __device__ __forceinline__ CoarseFold coarse_fold(const unsigned char* __restric
     for (int yy = 0; yy <= kCoarseCell; ++yy) {
       const int y = y0 + min(yy, wy - 1);
       const unsigned char* row = grid + (size_t)z * plane_bytes + (size_t)y * row_bytes;
-      v[zi][yy] = __builtin_nontemporal_load(reinterpret_cast<const U32x4*>(row + lane_off));
+      if constexpr (kRagged)
+        v[zi][yy] = __builtin_nontemporal_load(reinterpret_cast<const U32x4Any*>(row + lane_off));
+      else
+        v[zi][yy] = __builtin_nontemporal_load(reinterpret_cast<const U32x4*>(row + lane_off));
     }
   }
   CoarseFold f{__builtin_inff(), __builtin_inff(), 0u, 0u};
@@ -1577,29 +1553,36 @@ __device__ __forceinline__ CoarseFold coarse_fold(const unsigned char* __restric
   for (int j = 0; j < kP * (kCoarseCell + 1); ++j) {
     const U32x4& vj = v[j / (kCoarseCell + 1)][j % (kCoarseCell + 1)];
     const uint32_t wd[4] = {vj[0], vj[1], vj[2], vj[3]};
+    float x[kCols];
 #pragma unroll
     for (int c = 0; c < kCols; ++c) {
-      float x;
       if constexpr (kElemBytes == 4) {
-        x = __uint_as_float(wd[c]);
+        x[c] = __uint_as_float(wd[c]);
       } else {
         const unsigned short h = (unsigned short)(wd[c >> 1] >> ((c & 1) * 16));
-        x = (float)__builtin_bit_cast(_Float16, h);
-      }
-      const uint32_t ab = __float_as_uint(x) & 0x7fffffffu;
-      f.mn = fminf(f.mn, x);
-      f.mxb = max(f.mxb, ab);
-      if (c == 0) {
-        f.fmn = fminf(f.fmn, x);
-        f.fmxb = max(f.fmxb, ab);
+        x[c] = (float)__builtin_bit_cast(_Float16, h);
       }
     }
+    float first = x[0];
+    if constexpr (kRagged) {
+#pragma unroll
+      for (int c = 1; c < kCols; ++c) first = before == c ? x[c] : first;
+#pragma unroll
+      for (int c = 0; c < kCols - 1; ++c) x[c] = c < before ? x[kCols - 1] : x[c];
+    }
+#pragma unroll
+    for (int c = 0; c < kCols; ++c) {
+      f.mn = fminf(f.mn, x[c]);
+      f.mxb = max(f.mxb, __float_as_uint(x[c]) & 0x7fffffffu);
+    }
+    f.fmn = fminf(f.fmn, first);
+    f.fmxb = max(f.fmxb, __float_as_uint(first) & 0x7fffffffu);
   }
   return f;
 }
 
 // Block b (b mod 8 = the XCD it runs on) of a wide-path job, with kWaves waves.
-template <int kElemBytes, int kWaves>
+template <int kElemBytes, int kWaves, bool kRagged = false>
 __device__ __forceinline__ void coarse_wide_block(const CoarseJob& J, int b) {
   constexpr int kCols = 16 / kElemBytes;                               // columns per group
   constexpr int kCells = (kCoarseChunkGroups - 1) * kCols / kCoarseCell;  // cells per chunk
@@ -1618,10 +1601,11 @@ __device__ __forceinline__ void coarse_wide_block(const CoarseJob& J, int b) {
   const int wy = min(y0 + kCoarseCell, ny - 1) - y0 + 1;
   const int wz = min(z0 + kCoarseCell, nz - 1) - z0 + 1;
   const int x0 = ch * kCells * kCoarseCell;                     // first column of the chunk
-  const int n_groups = nx / kCols;                              // groups per grid row
+  const int n_groups = (nx + kCols - 1) / kCols;                // groups per grid row
   const int tid = threadIdx.x;
   const int cx_last = min(ch * kCells + kCells, ncx) - 1;
-  if (coarse_axis_gap(J.ball.c[0], ch * kCells, cx_last, ncx) +
+  // Ragged rows are passed over as wholes (their other chunks have always had full bounds).
+  if (coarse_axis_gap(J.ball.c[0], kRagged ? 0 : ch * kCells, kRagged ? ncx - 1 : cx_last, ncx) +
           coarse_axis_gap(J.ball.c[1], cy, cy, ncy) +
           coarse_axis_gap(J.ball.c[2], cz, cz, J.ncz) >
       J.ball.r2) {
@@ -1635,16 +1619,18 @@ __device__ __forceinline__ void coarse_wide_block(const CoarseJob& J, int b) {
   const int s = __builtin_amdgcn_readfirstlane(tid / kCoarseChunkGroups);
   const int g = tid & (kCoarseChunkGroups - 1);
   const int gg = min(x0 / kCols + g, n_groups - 1);             // clamped group of the row
-  const uint32_t lane_off = (uint32_t)gg * 16u;
+  const int before = kRagged ? max(kCols * (gg + 1) - nx, 0) : 0;
+  const uint32_t lane_off = (uint32_t)gg * 16u - (uint32_t)before * kElemBytes;
   const size_t row_bytes = (size_t)nx * kElemBytes, plane_bytes = row_bytes * (size_t)ny;
   // The 9 planes of the window are dealt to the waves in turn: the first 9 mod kWaves
   // waves take one plane more than the others, so no plane is loaded twice.
   constexpr int kLo = (kCoarseCell + 1) / kWaves, kExtra = (kCoarseCell + 1) % kWaves;
   const CoarseFold f =
-      s < kExtra ? coarse_fold<kElemBytes, kLo + 1>(J.grid, plane_bytes, row_bytes, z0, wz, y0,
-                                                    wy, s, kWaves, lane_off)
-                 : coarse_fold<kElemBytes, kLo>(J.grid, plane_bytes, row_bytes, z0, wz, y0, wy,
-                                                s, kWaves, lane_off);
+      s < kExtra
+          ? coarse_fold<kElemBytes, kLo + 1, kRagged>(J.grid, plane_bytes, row_bytes, z0, wz, y0,
+                                                      wy, s, kWaves, lane_off, before)
+          : coarse_fold<kElemBytes, kLo, kRagged>(J.grid, plane_bytes, row_bytes, z0, wz, y0, wy,
+                                                  s, kWaves, lane_off, before);
   const float mn = f.mn, fmn = f.fmn;
   const uint32_t mxb = f.mxb, fmxb = f.fmxb;
   s_mn[s][g] = mn;
@@ -1685,6 +1671,11 @@ __device__ __forceinline__ void coarse_wide_block(const CoarseJob& J, int b) {
 template <int kElemBytes>
 __global__ __launch_bounds__(kCoarseWideThreads) void grid_coarse_min_wide_kernel(CoarseJob J) {
   coarse_wide_block<kElemBytes, kCoarseSubsets>(J, (int)blockIdx.x);
+}
+
+template <int kElemBytes>
+__global__ __launch_bounds__(kCoarseWideThreads) void grid_coarse_min_ragged_kernel(CoarseJob J) {
+  coarse_wide_block<kElemBytes, kCoarseSubsets, true>(J, (int)blockIdx.x);
 }
 
 // A plan step's merge blocks (the first n_k2 blocks) and the wide-path bounds of another
@@ -2409,8 +2400,6 @@ int launch_ogm(const DevRobot* robot, const OgmArgs& a, const float* depth, floa
 static bool wide_coarse_job(const void* grid, bool f16, int nx, int ny, int nz,
                             const CoarseBall& ball, float* out, CoarseJob& job) {
   const int elem = f16 ? 2 : 4;
-  if (((long long)nx * elem) % 16 != 0 || reinterpret_cast<uintptr_t>(grid) % 16 != 0)
-    return false;
   job.grid = static_cast<const unsigned char*>(grid);
   job.nx = nx;
   job.ny = ny;
@@ -2423,7 +2412,7 @@ static bool wide_coarse_job(const void* grid, bool f16, int nx, int ny, int nz,
   job.nwork = (int)((long long)job.nchunks * job.ncy * job.ncz);
   job.ball = ball;
   job.out = out;
-  return true;
+  return ((long long)nx * elem) % 16 == 0 && reinterpret_cast<uintptr_t>(grid) % 16 == 0;
 }
 
 int launch_grid_coarse_min(const void* grid, bool f16, int nx, int ny, int nz,
@@ -2436,16 +2425,18 @@ int launch_grid_coarse_min(const void* grid, bool f16, int nx, int ny, int nz,
   for (int a = 0; a < 3; ++a) ball.c[a] = ball_c ? ball_c[a] : 0.f;
   ball.r2 = ball_c ? ball_r2 : __builtin_inff();
   CoarseJob job;
-  if (wide_coarse_job(grid, f16, nx, ny, nz, ball, out, job)) {
+  const bool whole = wide_coarse_job(grid, f16, nx, ny, nz, ball, out, job);
+  if (nx * elem >= 16) {
     const long long blocks = (job.nwork + kXcds - 1) / kXcds * kXcds;
-    auto k = f16 ? grid_coarse_min_wide_kernel<2> : grid_coarse_min_wide_kernel<4>;
+    auto k = whole ? (f16 ? grid_coarse_min_wide_kernel<2> : grid_coarse_min_wide_kernel<4>)
+                   : (f16 ? grid_coarse_min_ragged_kernel<2> : grid_coarse_min_ragged_kernel<4>);
     hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(kCoarseWideThreads), 0,
                        (hipStream_t)stream, job);
   } else {
     const uint32_t bytes = (uint32_t)((long long)nx * ny * nz * elem);
-    auto k = f16 ? grid_coarse_min_kernel<2> : grid_coarse_min_kernel<4>;
-    hipLaunchKernelGGL(k, dim3((unsigned)((long long)ncy * ncz)), dim3(kCoarseThreads), 0,
-                       (hipStream_t)stream, grid, bytes, nx, ny, nz, ncx, ncy, ncz, ball, out);
+    auto k = f16 ? grid_coarse_min_short_kernel<2> : grid_coarse_min_short_kernel<4>;
+    hipLaunchKernelGGL(k, dim3((unsigned)((long long)ncy * ncz)), dim3(kWave), 0,
+                       (hipStream_t)stream, grid, bytes, nx, ny, nz, ncy, ncz, ball, out);
   }
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
