@@ -365,7 +365,7 @@ __device__ __forceinline__ void transform_lines(int* lds, int n, Load&& load, De
     __syncthreads();
   }
   // The minimiser at the unit's first output, over the whole line (the first unit's is
-  // bounded by row 0 instead), eight reads in flight.
+  // bounded by row 0 instead), the next eight rows in flight.
   if (row0 > 0 && row0 < n) {
     int best = 0x7FFFFFFF;
     const int dt = 2 - (row0 << (kShift + 1));  // row q adds q dt: (p^2 - 2 p q) << kShift | 2 q, less p^2
@@ -374,14 +374,24 @@ __device__ __forceinline__ void transform_lines(int* lds, int n, Load&& load, De
     for (int c = 0; c < 8; ++c) ct[c] = opaque(c * dt);
     const int* r = col;
     int t = 0;
-    for (int left = n / 8; left > 0; --left, r += 8 * kLines) {
-      int g[8];
+    int g[8];
 #pragma unroll
-      for (int c = 0; c < 8; ++c) g[c] = r[c * kLines];
+    for (int c = 0; c < 8; ++c) g[c] = r[c * kLines];
+    for (int left = n / 8; left > 1; --left) {
+      r += 8 * kLines;
+      int next[8];
+#pragma unroll
+      for (int c = 0; c < 8; ++c) next[c] = r[c * kLines];
 #pragma unroll
       for (int c = 0; c < 8; c += 2) best = min3(best, g[c] + ct[c] + t, g[c + 1] + ct[c + 1] + t);
       t = opaque(t + 8 * dt);
+#pragma unroll
+      for (int c = 0; c < 8; ++c) g[c] = next[c];
     }
+#pragma unroll
+    for (int c = 0; c < 8; c += 2) best = min3(best, g[c] + ct[c] + t, g[c + 1] + ct[c + 1] + t);
+    t += 8 * dt;
+    r += 8 * kLines;
     for (int q = n & ~7; q < n; ++q, t += dt, r += kLines) best = min(best, r[0] + t);
     cut[team * kPer * kLines] = (Index)key_row(best);
   }
