@@ -57,7 +57,7 @@ static_assert((long long)kNoDist * kNoDist >= kNoneD &&
 //
 // A row is cut into runs of one kind; the distance is to the near end of the run on
 // either side.  A row lies on 16 lanes, kVox consecutive voxels on each: one or two
-// 16-byte loads, a bit per voxel that begins a run, a scan over the 16 lanes for the last
+// loads, a bit per voxel that begins a run, a scan over the 16 lanes for the last
 // begin to the left and the first one to the right, and from there along the lane's own
 // voxels two operations per voxel and side.  Rows begin at any byte, so loads and stores
 // are unaligned ones.  A voxel per lane (byte loads, four bit scans of 64-bit ballots per
@@ -83,7 +83,7 @@ template <int kVox>
 __global__ __launch_bounds__(64 * kRowWaves) void edt_pass_x_kernel(
     const uint8_t* __restrict__ occ, int nx, uint32_t rows, uint32_t nvox,
     uint16_t* __restrict__ xrec) {
-  static_assert(kVox == 16 || kVox == 32);
+  static_assert(kVox % 8 == 0 && kVox <= 32);
   const uint32_t row = blockIdx.x * kRowsPerBlock + threadIdx.x / kRowLanes;
   const int p0 = (threadIdx.x % kRowLanes) * kVox;  // the lane's first voxel
   const int own = row < rows ? nx - p0 : 0;         // voxels from there on
@@ -109,7 +109,7 @@ __global__ __launch_bounds__(64 * kRowWaves) void edt_pass_x_kernel(
   const uint32_t before = (uint32_t)from_left<1>((int)(m << (kVox - 1)), (int)m) >> (kVox - 1);
   uint32_t begin = m ^ ((m << 1) | (before & 1u));
   if (own < kVox) begin &= (1u << max(own, 0)) - 1u;
-  if (kVox == 16) begin &= 0xFFFFu;
+  if (kVox < 32) begin &= (1u << (kVox % 32)) - 1u;
 
   // The last begin in the lanes to the left, the first one in those to the right; kNoDist
   // and more away from any voxel of the row if there is none.
@@ -149,17 +149,17 @@ __global__ __launch_bounds__(64 * kRowWaves) void edt_pass_x_kernel(
     __builtin_memcpy(dst, out, 2 * kVox);
     return;
   }
-  // The row's last lane, of nx mod kVox voxels: the halves that are full, in turn.
+  // The row's last lane: the powers of two in its count, in turn.
 #pragma unroll
-  for (int h = kVox / 2; h >= 2; h /= 2) {
-    if (nx & h) {
+  for (int h = 16; h >= 2; h /= 2) {
+    if (h < kVox && (own & h)) {
       __builtin_memcpy(dst, out, 2 * h);
       dst += h;
 #pragma unroll
-      for (int i = 0; i < h / 2; ++i) out[i] = out[i + h / 2];
+      for (int i = 0; i < h / 2 && i + h / 2 < kVox / 2; ++i) out[i] = out[i + h / 2];
     }
   }
-  if (nx & 1) *dst = (uint16_t)out[0];
+  if (own & 1) *dst = (uint16_t)out[0];
 }
 
 // Whether x holds in any thread of the block (at most kWaves waves); a block barrier.
@@ -574,8 +574,12 @@ int launch_edt(const uint8_t* occ, int nx, int ny, int nz, float voxel, float* p
   uint16_t* xrec = reinterpret_cast<uint16_t*>(yrec + nvox);
   const long long rows = (long long)ny * nz;
   const uint32_t none_value = (uint32_t)nx * nx + (uint32_t)ny * ny + (uint32_t)nz * nz;
-  // 16 lanes of 16 voxels hold a row of up to 256, of 32 voxels one of up to 512.
-  const auto x_kernel = nx <= 256 ? edt_pass_x_kernel<16> : edt_pass_x_kernel<kEdtMaxSide / kRowLanes>;
+  // 16 lanes of 16 voxels hold a row of up to 256, of 24 one of up to 384, of 32 one of up
+  // to 512 (a 333-voxel row takes 14 lanes of 24 or 11 of 32: the field of 333x257x141 160.0
+  // and 161.4 us).
+  const auto x_kernel = nx <= 256   ? edt_pass_x_kernel<16>
+                        : nx <= 384 ? edt_pass_x_kernel<24>
+                                    : edt_pass_x_kernel<kEdtMaxSide / kRowLanes>;
   hipLaunchKernelGGL(x_kernel, dim3((unsigned)((rows + kRowsPerBlock - 1) / kRowsPerBlock)),
                      dim3(64 * kRowWaves), 0, stream, occ, nx, (uint32_t)rows, (uint32_t)nvox,
                      xrec);

@@ -1,5 +1,5 @@
 """The x pass of the distance field (16 lanes per row, 16 voxels per lane for rows of up to
-256 voxels, 32 for longer ones) at the row lengths where a lane, the last lane's stores or
+256 voxels, 24 up to 384, 32 for longer ones) at the row lengths where a lane, the last lane's stores or
 the voxels per lane change, with occupancy bytes of any non-zero value, the grid starting
 at any byte and ending with its buffer's data.  Every result is an integer, so the bound
 is equality."""
@@ -12,7 +12,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("nx", [1, 2, 3, 7, 8, 15, 16, 17, 31, 32, 33, 47, 48, 49, 63, 64, 127,
-                                240, 241, 255, 256, 257, 271, 272, 287, 288, 289, 496, 497, 511,
+                                240, 241, 255, 256, 257, 271, 272, 287, 288, 289, 333, 360,
+                                383, 384, 385, 496, 497, 511,
                                 512])
 def test_row_lengths(nx):
     import torch
