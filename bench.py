@@ -53,20 +53,20 @@ PEAK_FP32_TFLOPS = 157.3
 # reads half the bytes copied: x2; WRITE_SIZE reads them all: x1).  Valid only for
 # the kernel sources it was taken on: bench.py reports null traffic when their
 # hash differs.
-ROLLOUT_TRAFFIC = {"sources_sha256": "188e26cae7c3a2936ac4d546c21edf32063817c72ba26a689ab890931367897c",
-                   "fetch_kib": 2740.7, "fetch_scale": 2.0,
-                   "write_kib": 853.8, "write_scale": 1.0}
+ROLLOUT_TRAFFIC = {"sources_sha256": "b27dd4235de2522632998b7516d6754fd8ec5b6dcfc8d9ecf647b1bb29b5b58f",
+                   "fetch_kib": 2692.0, "fetch_scale": 2.0,
+                   "write_kib": 854.0, "write_scale": 1.0}
 # The same for one occupancy update (pixel and voxel pass together) at 200^3, 640x480.
-OGM_TRAFFIC = {"sources_sha256": "188e26cae7c3a2936ac4d546c21edf32063817c72ba26a689ab890931367897c",
-               "fetch_kib": 673.8 + 20301.4, "fetch_scale": 2.0,
-               "write_kib": 1200.5 + 39062.5, "write_scale": 1.0}
+OGM_TRAFFIC = {"sources_sha256": "b27dd4235de2522632998b7516d6754fd8ec5b6dcfc8d9ecf647b1bb29b5b58f",
+               "fetch_kib": 672.0 + 20375.0, "fetch_scale": 2.0,
+               "write_kib": 1200.0 + 9773.0, "write_scale": 1.0}
 
 
 # L2 requests of one rollout-cost launch on the default workload (rocprofv3 --pmc
 # TCC_REQ_sum, per dispatch), taken on the kernel sources named by the hash.  The L2
 # side of the roofline counts 128 B per request against the L2 peak of
 # PEAK_L2_GBPS: 8 XCDs x 16 channels x 128 B per clock x 2.4 GHz.
-ROLLOUT_L2 = {"sources_sha256": "188e26cae7c3a2936ac4d546c21edf32063817c72ba26a689ab890931367897c", "tcc_req": 226746.3}
+ROLLOUT_L2 = {"sources_sha256": "b27dd4235de2522632998b7516d6754fd8ec5b6dcfc8d9ecf647b1bb29b5b58f", "tcc_req": 203407.0}
 PEAK_L2_GBPS = 8 * 16 * 128 * 2.4
 
 
@@ -262,9 +262,9 @@ EDT_BYTES_PER_VOXEL = 5.0
 # HBM traffic of one construction at 200^3 (reactive scene; the three kernels together),
 # counted and scaled as ROLLOUT_TRAFFIC, valid for the sources named.
 EDT_TRAFFIC = {"sources": ("smpc_edt.hip", "smpc_internal.h"),
-               "sources_sha256": "119e5d909baa710898ce1b79cae4da3b9b58fdbe07621595edc881dfe20977b3",
-               "fetch_kib": 4090.6 + 33223.0 + 31089.6, "fetch_scale": 2.0,
-               "write_kib": 15625.0 + 33071.8 + 33859.8, "write_scale": 1.0}
+               "sources_sha256": "8a32108e50e2a7c55af9ea6b3c46f51b21313ae6ea86efb7dfefae3d90bdcded",
+               "fetch_kib": 4087.0 + 10751.0 + 15708.0, "fetch_scale": 2.0,
+               "write_kib": 15625.0 + 32481.0 + 32272.0, "write_scale": 1.0}
 PEAK_HBM_GBPS = 8000.0
 
 
