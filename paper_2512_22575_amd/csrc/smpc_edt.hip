@@ -209,16 +209,18 @@ static_assert(((long long)kFar + (kEdtMaxSide + kPad) * (kEdtMaxSide + kPad)) <<
 // A team stages one unit of kPer leaves of its block's lines and searches the minimiser at
 // the unit's first output over the whole line; the cuts in between and the leaves are
 // dealt to the teams in turn (obstacles and far regions cover neighbouring outputs).
-// kPer = 1, 2, 4 for lines of up to 64, 256 and 512 samples, at most eight waves per
+// kPer = 1, 2, 4 for lines of up to 64, 384 and 512 samples, at most twelve waves per
 // block: small grids still fill the chip, and a block inside an obstacle, which the pass
-// ends with, has twice the waves that kPer = 4 gives it at 200 samples (field of 200^3: 103.1 us;
-// kPer = 4 from 129 samples on: 104.8).
+// ends with, has twice the waves that kPer = 4 gives it.  Fields with kPer = 4 and with 2:
+// 200^3 104.8 and 103.1 us, 300x300x100 146 and 139, 64x128x400 61.6 and 59.3; 200x512x64, where
+// every block scans its lines 32 times, 95.8 and 101.7.
 __host__ __device__ constexpr int line_leaves(int n) { return (n + kLeaf - 1) / kLeaf; }
-__host__ __device__ constexpr int unit_leaves(int n) { return n <= 64 ? 1 : n <= 256 ? 2 : 4; }
+__host__ __device__ constexpr int unit_leaves(int n) { return n <= 64 ? 1 : n <= 384 ? 2 : 4; }
 __host__ __device__ constexpr int line_waves(int n) {
   return ((line_leaves(n) + unit_leaves(n) - 1) / unit_leaves(n) + 1) / 2;
 }
-constexpr int kMaxWaves = line_waves(kEdtMaxSide);  // 8
+constexpr int kMaxWaves = line_waves(384);  // 12
+static_assert(line_waves(256) <= kMaxWaves && line_waves(kEdtMaxSide) <= kMaxWaves, "most waves");
 
 // LDS of a block: the padded tile, then the minimisers at the cuts (Index: uint8_t for
 // lines of at most 256 samples, else uint16_t).
@@ -547,9 +549,11 @@ void launch_line_passes(const uint16_t* xrec, uint32_t* yrec, int nx, int ny, in
                         const FieldOut& fo, hipStream_t stream) {
   const auto y = ny <= 64    ? launch_pass_y<1, uint8_t>
                  : ny <= 256 ? launch_pass_y<2, uint8_t>
+                 : ny <= 384 ? launch_pass_y<2, uint16_t>
                              : launch_pass_y<4, uint16_t>;
   const auto z = nz <= 64    ? launch_pass_z<1, uint8_t>
                  : nz <= 256 ? launch_pass_z<2, uint8_t>
+                 : nz <= 384 ? launch_pass_z<2, uint16_t>
                              : launch_pass_z<4, uint16_t>;
   y(xrec, yrec, nx, ny, nz, stream);
   z(yrec, nx, ny, nz, fo, stream);

@@ -1,6 +1,6 @@
 """The y and z passes of the distance field at the sizes where their work split changes:
-lines of 64 / 65, 128 / 129, 256 / 257 and 512 samples (8, 16 or 32 outputs per unit, 8-
-or 16-bit row indices), whole and partial units of 8 outputs, and line counts around the
+lines of 64 / 65, 256 / 257, 384 / 385 and 512 samples (8, 16 or 32 outputs per unit, 8- or
+16-bit row indices), whole and partial units of 8 outputs, and line counts around the
 32 lines of a block.  Every result is an integer, so the bound is equality."""
 import numpy as np
 import pytest
@@ -25,7 +25,8 @@ def _scenes(n_z, n_y, n_x, axis, seed):
     return sparse, ~sparse, slab
 
 
-@pytest.mark.parametrize("n", [1, 7, 8, 9, 63, 64, 65, 127, 128, 129, 255, 256, 257, 511, 512])
+@pytest.mark.parametrize("n", [1, 7, 8, 9, 63, 64, 65, 127, 128, 129, 255, 256, 257, 383, 384, 385, 511,
+                               512])
 @pytest.mark.parametrize("axis", [0, 1])
 def test_line_lengths(n, axis):
     other, n_x = (3, 11) if n % 2 else (2, 16)   # 33 lines, or 32
