@@ -262,9 +262,9 @@ EDT_BYTES_PER_VOXEL = 5.0
 # HBM traffic of one construction at 200^3 (reactive scene; the three kernels together),
 # counted and scaled as ROLLOUT_TRAFFIC, valid for the sources named.
 EDT_TRAFFIC = {"sources": ("smpc_edt.hip", "smpc_internal.h"),
-               "sources_sha256": "8a32108e50e2a7c55af9ea6b3c46f51b21313ae6ea86efb7dfefae3d90bdcded",
-               "fetch_kib": 4087.0 + 10751.0 + 15708.0, "fetch_scale": 2.0,
-               "write_kib": 15625.0 + 32481.0 + 32272.0, "write_scale": 1.0}
+               "sources_sha256": "c0fad9e8cd3a64ee11a5c7a1a17298294f8a6a8e46f1d8e9c0f98e1442b9f26c",
+               "fetch_kib": 4091.0 + 10746.0 + 15704.0, "fetch_scale": 2.0,
+               "write_kib": 15625.0 + 32470.0 + 32286.0, "write_scale": 1.0}
 PEAK_HBM_GBPS = 8000.0
 
 
