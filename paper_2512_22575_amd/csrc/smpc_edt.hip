@@ -30,6 +30,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "smpc_internal.h"
 
@@ -162,16 +163,18 @@ __global__ __launch_bounds__(64 * kRowWaves) void edt_pass_x_kernel(
   if (own & 1) *dst = (uint16_t)out[0];
 }
 
-// Whether x holds in any thread of the block (at most kWaves waves); a block barrier.
+// The flags of all threads of the block (at most kWaves waves) or'ed; a block barrier.  Call
+// sites that can follow one another without a barrier have their own kSite.
 // (__syncthreads_or costs this kernel about 40 registers and two more barriers.)
-template <int kWaves>
-__device__ __forceinline__ bool block_any(bool x) {
-  __shared__ uint32_t waves_any[kWaves];
+template <int kWaves, int kSite>
+__device__ __forceinline__ uint32_t block_or(bool bit0, bool bit1) {
+  __shared__ uint32_t waves_or[kWaves];
   const int lane = threadIdx.x & 63;
-  const bool any = __any(x);
-  if (lane == 0) waves_any[threadIdx.x / 64] = any;
+  const uint32_t mine = (__any(bit0) ? 1u : 0u) | (__any(bit1) ? 2u : 0u);
+  if (lane == 0) waves_or[threadIdx.x / 64] = mine;
   __syncthreads();
-  return __any(lane < (int)(blockDim.x / 64) && waves_any[min(lane, kWaves - 1)] != 0u);
+  const uint32_t w = lane < (int)(blockDim.x / 64) ? waves_or[min(lane, kWaves - 1)] : 0u;
+  return (__any(w & 1u) ? 1u : 0u) | (__any(w & 2u) ? 2u : 0u);
 }
 
 // ---------------------------------------------------------------------------
@@ -200,6 +203,7 @@ __device__ __forceinline__ bool block_any(bool x) {
 constexpr int kLines = 32;              // lines per block, one per lane of a team
 constexpr int kLeaf = 8;                // outputs between two cuts
 constexpr int kPad = 3;                 // rows of "no sample" after a line
+constexpr int kTry = 8, kReach = 64;    // rows the D_in search goes out from a leaf (below)
 constexpr int kShift = 10;
 constexpr int kFar = kNoDist * kNoDist;  // sample of a padding row
 static_assert((2ll * (kEdtMaxSide - 1) + 1) < (1 << kShift), "q and the flag fit the low bits");
@@ -308,15 +312,29 @@ __device__ __forceinline__ void transform_lines(int* lds, int n, Load&& load, De
     cut[0] = 0;                            // minimisers before the first cut and after the
     cut[nleaf * kLines] = (Index)(n - 1);  // last one: the ends of the line bound them
   }
+  constexpr uint32_t kAllRows = 0xFFFFFFFFu >> (32 - kRows);
+  const uint32_t kinds = block_or<kMaxWaves, 0>(occ_rows != 0u, occ_rows != kAllRows);
+  const bool any_occ = kinds & 1u, any_free = kinds & 2u;
   // D_in at the occupied voxels, f_in being 0 on free ones: the rows of a leaf first, then
-  // outward from it (obstacles are thin against a line) until no farther row can matter to
+  // outward from it (most obstacles are thin against a line) until no farther row can matter to
   // any lane.  A row index clamped into the line is a candidate at more than its true
   // cost, which changes nothing.  Blocks inside obstacles are the last to end, and this is
   // what they spend their time on: with the test of the reach before each pair of rows, and
   // no loop before it, the 200^3 passes went from 53 and 57 us to 49 and 54.
-  if (block_any<kMaxWaves>(occ_rows != 0u)) {
-    for (int i = team; i < nleaf; i += teams) {
-      const int p0 = i * kLeaf;
+  //
+  // After kTry rows the minima found bound the rest of the search: a leaf that could go on
+  // beyond kReach rows (the middle of a solid of some 130 voxels and more; a floor's or wall's
+  // own plane, where a line has no free voxel and no sample) ends here, and its block, now
+  // "deep", gets these leaves' D_in from the scan that gives D_out, in time that does not
+  // grow with the thickness.  Without that, 200^3 took 446 us with every voxel occupied and
+  // 414 with one free, 64x512x200 (planes, rows, columns) with one occupied plane 323; now
+  // 95, 114 and 80.  kReach: 200^3 seen through a camera cone 164, 178, 188 us at 32, 48, 64
+  // rows, with a solid cube of 100 voxels 109, 110, 91 (the search alone: 271 and 89).
+  bool deep = false;   // block: some leaf is left to the scan
+  uint32_t todo = 0u;  // bit k: the team's k-th leaf is, in this lane
+  if (any_occ) {
+    for (int turn = 0; team + turn * teams < nleaf; ++turn) {
+      const int i = team + turn * teams, p0 = i * kLeaf;
       int own[kLeaf], acc[kLeaf], most = -1;  // own: f_in at occupied voxels, negative at free ones
 #pragma unroll
       for (int j = 0; j < kLeaf; ++j) own[j] = ~col[min(p0 + j, n - 1) * kLines];
@@ -332,12 +350,17 @@ __device__ __forceinline__ void transform_lines(int* lds, int n, Load&& load, De
                         max(own[k + 1], 0) + (j - k - 1) * (j - k - 1));
       }
       const int dmax = max(p0, n - p0 - kLeaf);  // rows on the longer side
+      bool far = false;
       for (int d = 1; d <= dmax; d += 2) {
         // Every output's rows nearer than d are in.
         int worst = acc[0];
 #pragma unroll
         for (int j = 1; j < kLeaf; ++j) worst = max(worst, acc[j]);
         if (worst <= d * d) break;
+        if (d == kTry + 1 && worst > kReach * kReach) {
+          far = true;
+          break;
+        }
         int f[4];
         f[0] = col[max(p0 - d, 0) * kLines];
         f[1] = col[max(p0 - d - 1, 0) * kLines];
@@ -352,13 +375,120 @@ __device__ __forceinline__ void transform_lines(int* lds, int n, Load&& load, De
           acc[j] = min3(acc[j], f[2] + hi * hi, f[3] + (hi + 1) * (hi + 1));
         }
       }
+      if (far) {
+        todo |= 1u << turn;
+        continue;
+      }
 #pragma unroll
       for (int j = 0; j < kLeaf; ++j) {
         const int p = p0 + j;
         if (p < n && own[j] >= 0) emit(p, (uint32_t)acc[j], true);
       }
     }
+    deep = block_or<kMaxWaves, 1>(todo != 0u, false) != 0u;
+  }
+
+  // The tile of a field's samples, which are 0 on its sources, marked by bit 0; the records
+  // are read a second time.
+  auto fill = [&](bool in) {
+    int first = row0;  // opaque: the loads are not those of the staging, kept in registers
+    asm volatile("" : "+v"(first));
+    constexpr int kAtOnce = kRows < 16 ? kRows : 16;
+#pragma unroll 1
+    for (int k0 = 0; k0 < kRows; k0 += kAtOnce) {
+      decltype(load(0)) v[kAtOnce];
+#pragma unroll
+      for (int k = 0; k < kAtOnce; ++k) v[k] = load(min(first + k0 + k, n - 1));
+#pragma unroll
+      for (int k = 0; k < kAtOnce; ++k) {
+        const int q = min(first + k0 + k, n - 1);
+        bool occ = false;
+        const int x = opaque((int)decode(v[k], occ));
+        const int q2 = __mul24(q, q);
+        col[q * kLines] = occ == in ? (x + q2) << kShift : (q2 << kShift) | 1;
+      }
+    }
+  };
+  // The leaves between cuts: those left to it (D_in) or all (D_out).
+  auto scan = [&](auto field) {
+    constexpr bool in = decltype(field)::value;
+    // The minimiser at the unit's first output, over the whole line (the first unit's is
+    // bounded by row 0 instead), the next eight rows in flight.
+    if (row0 > 0 && row0 < n) {
+      int best = 0x7FFFFFFF;
+      const int dt = 2 - (row0 << (kShift + 1));  // row q adds q dt: (p^2 - 2 p q) << kShift | 2 q, less p^2
+      int ct[8];
+#pragma unroll
+      for (int c = 0; c < 8; ++c) ct[c] = opaque(c * dt);
+      const int* r = col;
+      int t = 0;
+      int g[8];
+#pragma unroll
+      for (int c = 0; c < 8; ++c) g[c] = r[c * kLines];
+      for (int left = n / 8; left > 1; --left) {
+        r += 8 * kLines;
+        int next[8];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) next[c] = r[c * kLines];
+#pragma unroll
+        for (int c = 0; c < 8; c += 2) best = min3(best, g[c] + ct[c] + t, g[c + 1] + ct[c + 1] + t);
+        t = opaque(t + 8 * dt);
+#pragma unroll
+        for (int c = 0; c < 8; ++c) g[c] = next[c];
+      }
+#pragma unroll
+      for (int c = 0; c < 8; c += 2) best = min3(best, g[c] + ct[c] + t, g[c + 1] + ct[c + 1] + t);
+      t += 8 * dt;
+      r += 8 * kLines;
+      for (int q = n & ~7; q < n; ++q, t += dt, r += kLines) best = min(best, r[0] + t);
+      cut[team * kPer * kLines] = (Index)key_row(best);
+    }
     __syncthreads();
+
+    // The other cuts, by halving, each between its neighbours' minimisers.
+#pragma unroll
+    for (int s = kPer / 2; s >= 1; s >>= 1) {
+      for (int i = (2 * team + 1) * s; i < nleaf; i += 2 * teams * s) {
+        const int lo = cut[(i - s) * kLines], hi = cut[min(i + s, nleaf) * kLines];
+        int key = 0x7FFFFFFF;
+        const int s1 = 2 - ((i * kLeaf) << (kShift + 1)), s2 = 2 * s1, s3 = 3 * s1;
+        for (int q = lo; q <= hi; q += 4) {
+          const int* r = col + q * kLines;
+          const int m = __mul24(q, s1);
+          key = min3(key, r[0] + m, r[kLines] + m + s1);
+          key = min3(key, r[2 * kLines] + m + s2, r[3 * kLines] + m + s3);
+        }
+        cut[i * kLines] = (Index)min(key_row(key), hi);
+      }
+      __syncthreads();
+    }
+
+    for (int turn = 0; team + turn * teams < nleaf; ++turn) {
+      if (in && !(todo & (1u << turn))) continue;
+      const int i = team + turn * teams, p0 = i * kLeaf;
+      int acc[kLeaf];
+      leaf_minima(col, p0, cut[i * kLines], cut[(i + 1) * kLines], acc);
+      int own[kLeaf];
+#pragma unroll
+      for (int j = 0; j < kLeaf; ++j) own[j] = col[min(p0 + j, n - 1) * kLines];
+#pragma unroll
+      for (int j = 0; j < kLeaf; ++j) {
+        const int p = p0 + j;
+        if (p < n && !(own[j] & 1))
+          emit(p, (uint32_t)(acc[j] + (__mul24(p, p) << kShift)) >> kShift, in);
+      }
+    }
+  };
+  if (deep) {
+    fill(true);
+    __syncthreads();
+    scan(std::true_type{});
+    if (any_free) {
+      __syncthreads();
+      fill(false);
+      __syncthreads();
+    }
+  } else if (any_occ) {
     // The occupied voxels become D_out's sources (sample 0), marked by bit 0.
     for (uint32_t rows = occ_rows; rows != 0u; rows &= rows - 1u) {
       const int q = min(row0 + kRows - 1 - __builtin_ctz(rows), n - 1);
@@ -366,71 +496,7 @@ __device__ __forceinline__ void transform_lines(int* lds, int n, Load&& load, De
     }
     __syncthreads();
   }
-  // The minimiser at the unit's first output, over the whole line (the first unit's is
-  // bounded by row 0 instead), the next eight rows in flight.
-  if (row0 > 0 && row0 < n) {
-    int best = 0x7FFFFFFF;
-    const int dt = 2 - (row0 << (kShift + 1));  // row q adds q dt: (p^2 - 2 p q) << kShift | 2 q, less p^2
-    int ct[8];
-#pragma unroll
-    for (int c = 0; c < 8; ++c) ct[c] = opaque(c * dt);
-    const int* r = col;
-    int t = 0;
-    int g[8];
-#pragma unroll
-    for (int c = 0; c < 8; ++c) g[c] = r[c * kLines];
-    for (int left = n / 8; left > 1; --left) {
-      r += 8 * kLines;
-      int next[8];
-#pragma unroll
-      for (int c = 0; c < 8; ++c) next[c] = r[c * kLines];
-#pragma unroll
-      for (int c = 0; c < 8; c += 2) best = min3(best, g[c] + ct[c] + t, g[c + 1] + ct[c + 1] + t);
-      t = opaque(t + 8 * dt);
-#pragma unroll
-      for (int c = 0; c < 8; ++c) g[c] = next[c];
-    }
-#pragma unroll
-    for (int c = 0; c < 8; c += 2) best = min3(best, g[c] + ct[c] + t, g[c + 1] + ct[c + 1] + t);
-    t += 8 * dt;
-    r += 8 * kLines;
-    for (int q = n & ~7; q < n; ++q, t += dt, r += kLines) best = min(best, r[0] + t);
-    cut[team * kPer * kLines] = (Index)key_row(best);
-  }
-  __syncthreads();
-
-  // The other cuts, by halving, each between its neighbours' minimisers.
-#pragma unroll
-  for (int s = kPer / 2; s >= 1; s >>= 1) {
-    for (int i = (2 * team + 1) * s; i < nleaf; i += 2 * teams * s) {
-      const int lo = cut[(i - s) * kLines], hi = cut[min(i + s, nleaf) * kLines];
-      int key = 0x7FFFFFFF;
-      const int s1 = 2 - ((i * kLeaf) << (kShift + 1)), s2 = 2 * s1, s3 = 3 * s1;
-      for (int q = lo; q <= hi; q += 4) {
-        const int* r = col + q * kLines;
-        const int m = __mul24(q, s1);
-        key = min3(key, r[0] + m, r[kLines] + m + s1);
-        key = min3(key, r[2 * kLines] + m + s2, r[3 * kLines] + m + s3);
-      }
-      cut[i * kLines] = (Index)min(key_row(key), hi);
-    }
-    __syncthreads();
-  }
-
-  for (int i = team; i < nleaf; i += teams) {
-    const int p0 = i * kLeaf;
-    int acc[kLeaf];
-    leaf_minima(col, p0, cut[i * kLines], cut[(i + 1) * kLines], acc);
-    int own[kLeaf];
-#pragma unroll
-    for (int j = 0; j < kLeaf; ++j) own[j] = col[min(p0 + j, n - 1) * kLines];
-#pragma unroll
-    for (int j = 0; j < kLeaf; ++j) {
-      const int p = p0 + j;
-      if (p < n && !(own[j] & 1))
-        emit(p, (uint32_t)(acc[j] + (__mul24(p, p) << kShift)) >> kShift, false);
-    }
-  }
+  if (any_free) scan(std::false_type{});  // else no voxel takes D_out
 }
 
 // Block b's tile.  Blocks are dispatched to XCD b mod 8; the G neighbouring tiles that
@@ -511,10 +577,12 @@ struct FieldOut {
   }
 };
 
-// Pass z: block = 32 consecutive lines (y, x); writes the outputs.
+// Pass z: block = 32 consecutive lines (y, x); writes the outputs.  At 81 scalar registers
+// (what it takes without the limit) fewer waves fit a SIMD: 200^3 with no obstacle 67 us
+// instead of 66.
 template <int kPer, class Index>
-__global__ __launch_bounds__(64 * kMaxWaves) void edt_pass_z_kernel(
-    const uint32_t* __restrict__ yrec, int nx, int ny, int nz, FieldOut fo) {
+__global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_num_sgpr(80)))
+void edt_pass_z_kernel(const uint32_t* __restrict__ yrec, int nx, int ny, int nz, FieldOut fo) {
   extern __shared__ int lds[];
   const uint32_t plane = (uint32_t)nx * ny, tile = xcd_tile<kGroup>();
   if (tile * kLines >= plane) return;  // whole block
