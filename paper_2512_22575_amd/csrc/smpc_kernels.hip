@@ -1517,10 +1517,12 @@ struct CoarseJob {
 //
 // kRagged: rows that are not whole groups, or do not start on a 16-byte boundary, with
 // unaligned loads.  The row's last group is loaded so that it ends with the row: its first `before`
-// columns are the previous group's, and the row's last column takes their places.  A
-// block per row of cells, a voxel per lane and load, 27 loads at once, took 8.1 us of a
-// 150x150x25 grid; this takes 4.2.  Rows of whole groups keep their own kernel, which does
-// without the selects and is the one that plan steps launch with their rollouts or merge.
+// columns are the previous group's and are left out once the rows are folded, column by column
+// (selecting the columns in every row took 167 registers of float16: 400x400x25 38.9 us, 20.6
+// now).  A block per row of cells, a voxel per lane and load, 27 loads at once, took 8.1 us of
+// a 150x150x25 grid of float32; this takes 3.8.  Rows of whole groups keep their own kernel,
+// which does with four accumulators and is the one that plan steps launch with their rollouts
+// or merge.
 struct CoarseFold {
   float mn, fmn;
   uint32_t mxb, fmxb;
@@ -1549,34 +1551,48 @@ __device__ __forceinline__ CoarseFold coarse_fold(const unsigned char* __restric
     }
   }
   CoarseFold f{__builtin_inff(), __builtin_inff(), 0u, 0u};
+  float cmn[kCols];  // kRagged: each column's own minimum and maximum
+  uint32_t cmxb[kCols];
+#pragma unroll
+  for (int c = 0; c < kCols; ++c) {
+    cmn[c] = __builtin_inff();
+    cmxb[c] = 0u;
+  }
 #pragma unroll
   for (int j = 0; j < kP * (kCoarseCell + 1); ++j) {
     const U32x4& vj = v[j / (kCoarseCell + 1)][j % (kCoarseCell + 1)];
     const uint32_t wd[4] = {vj[0], vj[1], vj[2], vj[3]};
-    float x[kCols];
 #pragma unroll
     for (int c = 0; c < kCols; ++c) {
+      float x;
       if constexpr (kElemBytes == 4) {
-        x[c] = __uint_as_float(wd[c]);
+        x = __uint_as_float(wd[c]);
       } else {
         const unsigned short h = (unsigned short)(wd[c >> 1] >> ((c & 1) * 16));
-        x[c] = (float)__builtin_bit_cast(_Float16, h);
+        x = (float)__builtin_bit_cast(_Float16, h);
+      }
+      const uint32_t ab = __float_as_uint(x) & 0x7fffffffu;
+      if constexpr (kRagged) {
+        cmn[c] = fminf(cmn[c], x);
+        cmxb[c] = max(cmxb[c], ab);
+      } else {
+        f.mn = fminf(f.mn, x);
+        f.mxb = max(f.mxb, ab);
+        if (c == 0) {
+          f.fmn = fminf(f.fmn, x);
+          f.fmxb = max(f.fmxb, ab);
+        }
       }
     }
-    float first = x[0];
-    if constexpr (kRagged) {
-#pragma unroll
-      for (int c = 1; c < kCols; ++c) first = before == c ? x[c] : first;
-#pragma unroll
-      for (int c = 0; c < kCols - 1; ++c) x[c] = c < before ? x[kCols - 1] : x[c];
-    }
+  }
+  if constexpr (kRagged) {
 #pragma unroll
     for (int c = 0; c < kCols; ++c) {
-      f.mn = fminf(f.mn, x[c]);
-      f.mxb = max(f.mxb, __float_as_uint(x[c]) & 0x7fffffffu);
+      f.mn = fminf(f.mn, c < before ? __builtin_inff() : cmn[c]);
+      f.mxb = max(f.mxb, c < before ? 0u : cmxb[c]);
+      f.fmn = c == before ? cmn[c] : f.fmn;
+      f.fmxb = c == before ? cmxb[c] : f.fmxb;
     }
-    f.fmn = fminf(f.fmn, first);
-    f.fmxb = max(f.fmxb, __float_as_uint(first) & 0x7fffffffu);
   }
   return f;
 }
