@@ -25,8 +25,9 @@
 // per sample: split over 16 lanes per line they took 75 us (y) and 107 us (z) of a 200^3
 // field of 40 obstacles, at 150 VALU and as many SALU instructions per output.  They use
 // the other property of the same minimisation, that the minimiser over q moves right with
-// p (transform_lines): 48 and 53 us on the same grid.  All blocks of such a grid run at
-// once, and those inside obstacles end last (the slowest waves take twice the mean).
+// p (transform_lines): 48 and 53 us on the same grid.  Four blocks of seven waves fit a CU, so
+// 1024 of such a grid's 1250 run at once and the others as those end; blocks inside obstacles
+// take up to twice the mean time.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -188,9 +189,9 @@ __device__ __forceinline__ uint32_t block_or(bool bit0, bool bit1) {
 // output over the whole line, the ones between by halving, each between its neighbours'
 // minimisers; then the kLeaf outputs from one cut to the next scan the rows between the
 // two minimisers, with all their minima in registers.  A line of n outputs costs about
-// n^2 / 32 + 20 n pair evaluations instead of the n^2 of the definition, in loops without
-// data-dependent lists; all of it is integer arithmetic on 32-bit words, so the result is
-// exact.
+// n^2 / (8 kPer) + 20 n pair evaluations (kPer = 1, 2 or 4, below) instead of the n^2 of the
+// definition, in loops without data-dependent lists; all of it is integer arithmetic on 32-bit
+// words, so the result is exact.
 //
 // Tile words.  A D_out sample f(q) is stored as (f(q) + q^2) << kShift, from which
 // f(q) + (p - q)^2 follows by adding (p^2 - 2 p q) << kShift: one addition per pair.
@@ -327,9 +328,9 @@ __device__ __forceinline__ void transform_lines(int* lds, int n, Load&& load, De
   // own plane, where a line has no free voxel and no sample) ends here, and its block, now
   // "deep", gets these leaves' D_in from the scan that gives D_out, in time that does not
   // grow with the thickness.  Without that, 200^3 took 446 us with every voxel occupied and
-  // 414 with one free, 64x512x200 (planes, rows, columns) with one occupied plane 323; now
-  // 95, 114 and 80.  kReach: 200^3 seen through a camera cone 164, 178, 188 us at 32, 48, 64
-  // rows, with a solid cube of 100 voxels 109, 110, 91 (the search alone: 271 and 89).
+  // 414 with one free, 200x512x64 with one occupied xy plane 323; now 95, 114 and 80.
+  // kReach: 200^3 seen through a camera cone 164, 178, 188 us at 32, 48, 64 rows, with a
+  // solid cube of 100 voxels 109, 110, 91 (the search alone: 271 and 89).
   bool deep = false;   // block: some leaf is left to the scan
   uint32_t todo = 0u;  // bit k: the team's k-th leaf is, in this lane
   if (any_occ) {
@@ -416,7 +417,8 @@ __device__ __forceinline__ void transform_lines(int* lds, int n, Load&& load, De
     // bounded by row 0 instead), the next eight rows in flight.
     if (row0 > 0 && row0 < n) {
       int best = 0x7FFFFFFF;
-      const int dt = 2 - (row0 << (kShift + 1));  // row q adds q dt: (p^2 - 2 p q) << kShift | 2 q, less p^2
+      // Row q adds q dt: (p^2 - 2 p q) << kShift | 2 q, less p^2.
+      const int dt = 2 - (row0 << (kShift + 1));
       int ct[8];
 #pragma unroll
       for (int c = 0; c < 8; ++c) ct[c] = opaque(c * dt);

@@ -176,16 +176,17 @@ int launch_plan_step_bounds(const DevRobot* robot, const Request& q, const Launc
 // A batch of requests (device array `reqs`; block maps k1_map [k1_blocks], k2_map
 // [k2_blocks] and kf_map [kf_blocks] give each block's request index) as one HIP graph
 // (descriptor upload, the batch kernels -- the fold among them when `fold`, whether or not
-// this batch has fold blocks -- result download), created at the first launch and re-parameterised for every later one.  `*graph` is
-// the slot's handle (null before the first launch); the caller relaunches it only after
-// the previous launch has completed (a launch for a robot of the other pair kind, `far`,
-// or the other `fold` rebuilds the graph).  up: host -> device bytes (descriptors and maps);
-// res: device -> host result bytes.  Returns a hipError_t value.
+// this batch has fold blocks -- result download), created at the first launch and
+// re-parameterised for every later one.  `*graph` is the slot's handle (null before the first
+// launch); the caller relaunches it only after the previous launch has completed (a launch
+// for a robot of the other pair kind, `far`, or the other `fold` rebuilds the graph).
+// up: host -> device bytes (descriptors and maps); res: device -> host result bytes.
+// Returns a hipError_t value.
 int launch_batch_graph(void** graph, const DevRobot* robot, void* d_up, const void* h_up,
                        size_t up_bytes, const Request* reqs, const int32_t* k1_map,
                        int k1_blocks, const int32_t* k2_map, int k2_blocks, const int32_t* kf_map,
-                       int kf_blocks, size_t k1_lds, bool f16, bool far, bool fold, void* h_res, const void* d_res, size_t res_bytes,
-                       void* stream);
+                       int kf_blocks, size_t k1_lds, bool f16, bool far, bool fold, void* h_res,
+                       const void* d_res, size_t res_bytes, void* stream);
 void destroy_batch_graph(void* graph);
 
 // Disturbances of the sampling mode written to memory (eps [K][H][7], words [K][H][8];

@@ -2152,8 +2152,9 @@ __global__ __launch_bounds__(kOgmThreads) void ogm_voxel4_kernel(
     for (int j = 0; j < 4; ++j) bits |= (l[j] > a.l_occ ? 1u : 0u) << (8 * j);
     const uint32_t g = blk_g + tid + k * kOgmThreads;
     if (g < ngroups) {
-      // A group with no update and no reset keeps its values: 56 % of a 200^3 map is out of
-      // the reference camera's view, 18 MB of the 72 MB the pass would move.
+      // A group with no update and no reset keeps its values and is not stored (an observed one
+      // is, also where clamping leaves it as it was): 56 % of a 200^3 map is out of the view of
+      // a camera beside the arm, 18 of the 72 MB that this pass would move there.
       if (seen) L4[g] = make_float4(l[0], l[1], l[2], l[3]);
       if (occ) occ4[g] = bits;
     }
@@ -2317,8 +2318,8 @@ void destroy_batch_graph(void* handle) {
 int launch_batch_graph(void** handle, const DevRobot* robot, void* d_up, const void* h_up,
                        size_t up_bytes, const Request* reqs, const int32_t* k1_map,
                        int k1_blocks, const int32_t* k2_map, int k2_blocks, const int32_t* kf_map,
-                       int kf_blocks, size_t k1_lds, bool f16, bool far, bool fold, void* h_res, const void* d_res, size_t res_bytes,
-                       void* stream) {
+                       int kf_blocks, size_t k1_lds, bool f16, bool far, bool fold, void* h_res,
+                       const void* d_res, size_t res_bytes, void* stream) {
   void* f1 = f16 ? (far ? reinterpret_cast<void*>(rollout_cost_batch_kernel<2, true>)
                        : reinterpret_cast<void*>(rollout_cost_batch_kernel<2, false>))
                  : (far ? reinterpret_cast<void*>(rollout_cost_batch_kernel<4, true>)
@@ -2411,8 +2412,8 @@ int launch_ogm(const DevRobot* robot, const OgmArgs& a, const float* depth, floa
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-// The wide-path job for a grid, or false when its rows are not a multiple of 16 bytes
-// in a 16-byte-aligned grid.
+// Fills the bounds job of a grid; returns whether its rows are whole 16-byte groups in a
+// 16-byte-aligned grid (else the job is the ragged kernel's).
 static bool wide_coarse_job(const void* grid, bool f16, int nx, int ny, int nz,
                             const CoarseBall& ball, float* out, CoarseJob& job) {
   const int elem = f16 ? 2 : 4;
@@ -2433,10 +2434,8 @@ static bool wide_coarse_job(const void* grid, bool f16, int nx, int ny, int nz,
 
 int launch_grid_coarse_min(const void* grid, bool f16, int nx, int ny, int nz,
                            const float* ball_c, float ball_r2, float* out, void* stream) {
-  const int ncx = coarse_cells_1d(nx), ncy = coarse_cells_1d(ny), ncz = coarse_cells_1d(nz);
-  const long long ncells = (long long)ncx * ncy * ncz;
+  const int ncy = coarse_cells_1d(ny), ncz = coarse_cells_1d(nz);
   const int elem = f16 ? 2 : 4;
-  (void)ncells;
   CoarseBall ball;
   for (int a = 0; a < 3; ++a) ball.c[a] = ball_c ? ball_c[a] : 0.f;
   ball.r2 = ball_c ? ball_r2 : __builtin_inff();
