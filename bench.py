@@ -53,11 +53,11 @@ PEAK_FP32_TFLOPS = 157.3
 # reads half the bytes copied: x2; WRITE_SIZE reads them all: x1).  Valid only for
 # the kernel sources it was taken on: bench.py reports null traffic when their
 # hash differs.
-ROLLOUT_TRAFFIC = {"sources_sha256": "b27dd4235de2522632998b7516d6754fd8ec5b6dcfc8d9ecf647b1bb29b5b58f",
+ROLLOUT_TRAFFIC = {"sources_sha256": "3d80081d482a90b734f4f582ba9d4c04d446c36216d369ce2694d96fd867a833",
                    "fetch_kib": 2692.0, "fetch_scale": 2.0,
                    "write_kib": 854.0, "write_scale": 1.0}
 # The same for one occupancy update (pixel and voxel pass together) at 200^3, 640x480.
-OGM_TRAFFIC = {"sources_sha256": "b27dd4235de2522632998b7516d6754fd8ec5b6dcfc8d9ecf647b1bb29b5b58f",
+OGM_TRAFFIC = {"sources_sha256": "3d80081d482a90b734f4f582ba9d4c04d446c36216d369ce2694d96fd867a833",
                "fetch_kib": 672.0 + 20375.0, "fetch_scale": 2.0,
                "write_kib": 1200.0 + 9773.0, "write_scale": 1.0}
 
@@ -66,7 +66,7 @@ OGM_TRAFFIC = {"sources_sha256": "b27dd4235de2522632998b7516d6754fd8ec5b6dcfc8d9
 # TCC_REQ_sum, per dispatch), taken on the kernel sources named by the hash.  The L2
 # side of the roofline counts 128 B per request against the L2 peak of
 # PEAK_L2_GBPS: 8 XCDs x 16 channels x 128 B per clock x 2.4 GHz.
-ROLLOUT_L2 = {"sources_sha256": "b27dd4235de2522632998b7516d6754fd8ec5b6dcfc8d9ecf647b1bb29b5b58f", "tcc_req": 203407.0}
+ROLLOUT_L2 = {"sources_sha256": "3d80081d482a90b734f4f582ba9d4c04d446c36216d369ce2694d96fd867a833", "tcc_req": 204370.0}
 PEAK_L2_GBPS = 8 * 16 * 128 * 2.4
 
 
@@ -262,9 +262,9 @@ EDT_BYTES_PER_VOXEL = 5.0
 # HBM traffic of one construction at 200^3 (reactive scene; the three kernels together),
 # counted and scaled as ROLLOUT_TRAFFIC, valid for the sources named.
 EDT_TRAFFIC = {"sources": ("smpc_edt.hip", "smpc_internal.h"),
-               "sources_sha256": "c0fad9e8cd3a64ee11a5c7a1a17298294f8a6a8e46f1d8e9c0f98e1442b9f26c",
-               "fetch_kib": 4091.0 + 10746.0 + 15704.0, "fetch_scale": 2.0,
-               "write_kib": 15625.0 + 32470.0 + 32286.0, "write_scale": 1.0}
+               "sources_sha256": "1ef7b782825576e787cb20740cf9f78acf90df05df80558a8eca74bd9d5e2300",
+               "fetch_kib": 4092.0 + 10789.0 + 15748.0, "fetch_scale": 2.0,
+               "write_kib": 15625.0 + 32454.0 + 32290.0, "write_scale": 1.0}
 PEAK_HBM_GBPS = 8000.0
 
 
