@@ -2018,9 +2018,10 @@ __global__ __launch_bounds__(kOgmThreads) void ogm_voxel_kernel(
       }
     }
     const uint32_t o = loc + k * kOgmThreads;
-    if (seen)  // others keep their value
-      __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, l), lbuf, (int)(o * 4u),
-                                            0, 0);
+    // Others keep their value: a store past the buffer's end does nothing, and needs no branch
+    // (a branch per store made a 199^3 map wholly in view 25.7 us instead of 24.8).
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, l), lbuf,
+                                          (int)(seen ? o * 4u : nblk * 4u), 0, 0);
     if (occ)
       __builtin_amdgcn_raw_buffer_store_b8((uint8_t)(l > a.l_occ ? 1 : 0),
                                            ogm_buffer(occ + blk0, nblk), (int)o, 0, 0);
