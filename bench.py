@@ -53,11 +53,11 @@ PEAK_FP32_TFLOPS = 157.3
 # reads half the bytes copied: x2; WRITE_SIZE reads them all: x1).  Valid only for
 # the kernel sources it was taken on: bench.py reports null traffic when their
 # hash differs.
-ROLLOUT_TRAFFIC = {"sources_sha256": "3d80081d482a90b734f4f582ba9d4c04d446c36216d369ce2694d96fd867a833",
-                   "fetch_kib": 2692.0, "fetch_scale": 2.0,
+ROLLOUT_TRAFFIC = {"sources_sha256": "c94da207d567cac0583d50f0dd08ba2b2c861d82f462e14b9926db9cd0aa4883",
+                   "fetch_kib": 2695.0, "fetch_scale": 2.0,
                    "write_kib": 854.0, "write_scale": 1.0}
 # The same for one occupancy update (pixel and voxel pass together) at 200^3, 640x480.
-OGM_TRAFFIC = {"sources_sha256": "3d80081d482a90b734f4f582ba9d4c04d446c36216d369ce2694d96fd867a833",
+OGM_TRAFFIC = {"sources_sha256": "c94da207d567cac0583d50f0dd08ba2b2c861d82f462e14b9926db9cd0aa4883",
                "fetch_kib": 672.0 + 20375.0, "fetch_scale": 2.0,
                "write_kib": 1200.0 + 9773.0, "write_scale": 1.0}
 
@@ -66,7 +66,7 @@ OGM_TRAFFIC = {"sources_sha256": "3d80081d482a90b734f4f582ba9d4c04d446c36216d369
 # TCC_REQ_sum, per dispatch), taken on the kernel sources named by the hash.  The L2
 # side of the roofline counts 128 B per request against the L2 peak of
 # PEAK_L2_GBPS: 8 XCDs x 16 channels x 128 B per clock x 2.4 GHz.
-ROLLOUT_L2 = {"sources_sha256": "3d80081d482a90b734f4f582ba9d4c04d446c36216d369ce2694d96fd867a833", "tcc_req": 204370.0}
+ROLLOUT_L2 = {"sources_sha256": "c94da207d567cac0583d50f0dd08ba2b2c861d82f462e14b9926db9cd0aa4883", "tcc_req": 205868.0}
 PEAK_L2_GBPS = 8 * 16 * 128 * 2.4
 
 
