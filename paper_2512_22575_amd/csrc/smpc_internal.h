@@ -76,7 +76,7 @@ struct StepParams {
   int32_t nx, ny, nz;
   uint32_t grid_bytes;
   int32_t ncx, ncy, ncz;       // coarse bound cells per axis
-  uint32_t coarse_bytes;       // 0: no coarse bounds
+  uint32_t coarse_bytes;       // 0: no coarse bounds, or none that a state reads (H = 1)
   float cmax[3];               // ncx - 1, ncy - 1, ncz - 1
   float cstride[2];            // ncx, ncx * ncy (cell index strides)
   int32_t K, H, R, P;          // samples, horizon, rollouts per K1 block, K1 blocks

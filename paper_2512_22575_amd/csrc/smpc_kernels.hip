@@ -494,7 +494,7 @@ __device__ __forceinline__ float step_cost(const DevRobot* __restrict__ rob, con
     for (int s = l * kSpl; s < (l + 1) * kSpl; ++s)
       if (bound[s] >= p.env_thr[s]) need &= ~(1u << s);
   };
-  const bool bounded = p.coarse_bytes != 0u && p.H > 1;  // one step: only terminal states
+  const bool bounded = p.coarse_bytes != 0u;
   const Frame T = fk_spheres(rob, sc0, dq, px, py, pz, [&](int l) {
     if (!bounded) return;
 #pragma unroll

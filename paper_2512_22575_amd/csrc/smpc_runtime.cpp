@@ -256,8 +256,10 @@ StepParams make_params(const smpc_ctx* ctx, const smpc_plan_args* a, const Launc
   p.ncx = coarse_cells_1d(a->esdf.nx);
   p.ncy = coarse_cells_1d(a->esdf.ny);
   p.ncz = coarse_cells_1d(a->esdf.nz);
-  p.coarse_bytes =
-      a->esdf.coarse ? (uint32_t)((long long)p.ncx * p.ncy * p.ncz * (long long)sizeof(float)) : 0u;
+  // A single step has terminal states only, without collision terms: no bound is read.
+  p.coarse_bytes = a->esdf.coarse && a->H > 1
+                       ? (uint32_t)((long long)p.ncx * p.ncy * p.ncz * (long long)sizeof(float))
+                       : 0u;
   p.cmax[0] = (float)(p.ncx - 1);
   p.cmax[1] = (float)(p.ncy - 1);
   p.cmax[2] = (float)(p.ncz - 1);
