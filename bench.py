@@ -53,11 +53,11 @@ PEAK_FP32_TFLOPS = 157.3
 # reads half the bytes copied: x2; WRITE_SIZE reads them all: x1).  Valid only for
 # the kernel sources it was taken on: bench.py reports null traffic when their
 # hash differs.
-ROLLOUT_TRAFFIC = {"sources_sha256": "c94da207d567cac0583d50f0dd08ba2b2c861d82f462e14b9926db9cd0aa4883",
+ROLLOUT_TRAFFIC = {"sources_sha256": "d3fedf381fbe265d3f6bfbcc02ee601baf5b41d8a85032af4c9466e37356892a",
                    "fetch_kib": 2695.0, "fetch_scale": 2.0,
                    "write_kib": 854.0, "write_scale": 1.0}
 # The same for one occupancy update (pixel and voxel pass together) at 200^3, 640x480.
-OGM_TRAFFIC = {"sources_sha256": "c94da207d567cac0583d50f0dd08ba2b2c861d82f462e14b9926db9cd0aa4883",
+OGM_TRAFFIC = {"sources_sha256": "d3fedf381fbe265d3f6bfbcc02ee601baf5b41d8a85032af4c9466e37356892a",
                "fetch_kib": 672.0 + 20375.0, "fetch_scale": 2.0,
                "write_kib": 1200.0 + 9773.0, "write_scale": 1.0}
 
@@ -66,7 +66,7 @@ OGM_TRAFFIC = {"sources_sha256": "c94da207d567cac0583d50f0dd08ba2b2c861d82f462e1
 # TCC_REQ_sum, per dispatch), taken on the kernel sources named by the hash.  The L2
 # side of the roofline counts 128 B per request against the L2 peak of
 # PEAK_L2_GBPS: 8 XCDs x 16 channels x 128 B per clock x 2.4 GHz.
-ROLLOUT_L2 = {"sources_sha256": "c94da207d567cac0583d50f0dd08ba2b2c861d82f462e14b9926db9cd0aa4883", "tcc_req": 205868.0}
+ROLLOUT_L2 = {"sources_sha256": "d3fedf381fbe265d3f6bfbcc02ee601baf5b41d8a85032af4c9466e37356892a", "tcc_req": 206614.0}
 PEAK_L2_GBPS = 8 * 16 * 128 * 2.4
 
 
@@ -262,9 +262,9 @@ EDT_BYTES_PER_VOXEL = 5.0
 # HBM traffic of one construction at 200^3 (reactive scene; the three kernels together),
 # counted and scaled as ROLLOUT_TRAFFIC, valid for the sources named.
 EDT_TRAFFIC = {"sources": ("smpc_edt.hip", "smpc_internal.h"),
-               "sources_sha256": "1ef7b782825576e787cb20740cf9f78acf90df05df80558a8eca74bd9d5e2300",
+               "sources_sha256": "3b3bbbd387a8e30d5a449047db63a10f8171628cec34f5c2f22021d317472188",
                "fetch_kib": 4092.0 + 10789.0 + 15748.0, "fetch_scale": 2.0,
-               "write_kib": 15625.0 + 32454.0 + 32290.0, "write_scale": 1.0}
+               "write_kib": 15625.0 + 32465.0 + 32287.0, "write_scale": 1.0}
 PEAK_HBM_GBPS = 8000.0
 
 
